@@ -136,7 +136,7 @@ def traffic_from_profile(kernel, workload_name):
 
 
 ATTN_SOURCES = ("attention.hip", "device.h", "kernels.h")
-GEMM_SOURCES = ("gemm.hip", "gemm_tiled.hip", "gemm_pipe.hip", "gemm_slab.hip", "gemm_mx.hip", "gemm_epilogue.h", "device.h",
+GEMM_SOURCES = ("gemm.hip", "gemm_tiled.hip", "gemm_pipe.hip", "gemm_ring.hip", "gemm_slab.hip", "gemm_mx.hip", "gemm_epilogue.h", "device.h",
                 "kernels.h")
 KERNEL_SOURCES = {"attn_split": ATTN_SOURCES, "attn_prefill": ATTN_SOURCES, "qkv": GEMM_SOURCES,
                   "oproj": GEMM_SOURCES, "expert_gu": GEMM_SOURCES, "expert_down": GEMM_SOURCES,

@@ -260,6 +260,7 @@ hipError_t launch_gemm(int dtype, int expert_fmt, const Gemm& g, hipStream_t s) 
     if (tiled_gemm_applies(dtype, g)) return launch_gemm_tiled(expert_fmt, g, s);
     return hipErrorNotSupported;
   }
+  if (ring_gemm_applies(dtype, expert_fmt, g)) return launch_gemm_ring(expert_fmt, g, s);
   if (slab_gemm_applies(dtype, expert_fmt, g)) return launch_gemm_slab(expert_fmt, g, s);
   if (tiled_gemm_applies(dtype, g)) return launch_gemm_tiled(expert_fmt, g, s);
   if (expert_fmt != 0) return dtype == 1 ? gemm_dispatch_mxfp4(g, s) : hipErrorNotSupported;

@@ -119,6 +119,58 @@ __device__ __forceinline__ void store8(bf16* p, const float v[8]) {
       make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
 }
 
+// Token t's dims j0 .. j0 + 7 (lo) and d/2 + j0 .. (hi) of one projection head,
+// bias added: rotary embedding of q and k, q to the q buffer, k and v into
+// the token's page.
+template <typename T>
+__device__ __forceinline__ void qkv_store(const Gemm& P, int t, int head, int j0, float (&lo)[8], float (&hi)[8]) {
+  const int D = P.head_dim, half = D / 2;
+  const int pos = P.tok_pos[t];
+  if (head < P.hq + P.hkv) {  // q or k: rotate the pairs (j, j + d/2)
+    if (pos < 0 || pos >= P.rope_max_pos) {
+      set_error(P.err, 2);
+      return;
+    }
+    const float4* cp = reinterpret_cast<const float4*>(P.rope_cos + (int64_t)pos * half + j0);
+    const float4* sp = reinterpret_cast<const float4*>(P.rope_sin + (int64_t)pos * half + j0);
+    const float4 ca = cp[0], cb = cp[1], sa = sp[0], sb = sp[1];
+    const float cs[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
+    const float sn[8] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float a = lo[i], bb = hi[i];
+      lo[i] = a * cs[i] - bb * sn[i];
+      hi[i] = a * sn[i] + bb * cs[i];
+    }
+  }
+  if (head < P.hq) {
+    T* q = reinterpret_cast<T*>(P.q_out) + ((int64_t)t * P.hq + head) * D;
+    store8(q + j0, lo);
+    store8(q + j0 + half, hi);
+    return;
+  }
+  const int lp = pos >> 4;
+  const int seq = P.tok_seq[t];
+  const int page = (pos >= 0 && lp < P.max_pages) ? P.page_table[(int64_t)seq * P.max_pages + lp] : -1;
+  if (page < 0 || page >= P.n_pages) {
+    set_error(P.err, 1);
+    return;
+  }
+  const int slot = pos & 15;
+  if (head < P.hq + P.hkv) {
+    T* kp = reinterpret_cast<T*>(P.k_pool) + ((int64_t)page * P.hkv + (head - P.hq)) * PAGE * D;
+    store8(kp + k_off(slot, j0), lo);
+    store8(kp + k_off(slot, j0 + half), hi);
+  } else {
+    T* vp = reinterpret_cast<T*>(P.v_pool) + ((int64_t)page * P.hkv + (head - P.hq - P.hkv)) * PAGE * D;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      Elem<T>::store(vp, v_off(slot, j0 + i), lo[i]);
+      Elem<T>::store(vp, v_off(slot, j0 + half + i), hi[i]);
+    }
+  }
+}
+
 // cr[m * ld + n]: the finished fp32 tile for token rows m0 .. m0 + mrows - 1 and
 // the nblk 16-row weight blocks starting at blk0.
 // A thread's bias values in the SwiGLU and bias/residual epilogues: the same
@@ -181,50 +233,7 @@ __device__ void epilogue(const Gemm& P, const float* cr, int ld, int m0, int mro
           hi[i] = c[8 + i] + bb[8 + i];
         }
       }
-      const int pos = P.tok_pos[t];
-      if (head < P.hq + P.hkv) {  // q or k: rotate the pairs (j, j + d/2)
-        if (pos < 0 || pos >= P.rope_max_pos) {
-          set_error(P.err, 2);
-          continue;
-        }
-        const float4* cp = reinterpret_cast<const float4*>(P.rope_cos + (int64_t)pos * half + j0);
-        const float4* sp = reinterpret_cast<const float4*>(P.rope_sin + (int64_t)pos * half + j0);
-        const float4 ca = cp[0], cb = cp[1], sa = sp[0], sb = sp[1];
-        const float cs[8] = {ca.x, ca.y, ca.z, ca.w, cb.x, cb.y, cb.z, cb.w};
-        const float sn[8] = {sa.x, sa.y, sa.z, sa.w, sb.x, sb.y, sb.z, sb.w};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float a = lo[i], bb = hi[i];
-          lo[i] = a * cs[i] - bb * sn[i];
-          hi[i] = a * sn[i] + bb * cs[i];
-        }
-      }
-      if (head < P.hq) {
-        T* q = reinterpret_cast<T*>(P.q_out) + ((int64_t)t * P.hq + head) * D;
-        store8(q + j0, lo);
-        store8(q + j0 + half, hi);
-        continue;
-      }
-      const int lp = pos >> 4;
-      const int seq = P.tok_seq[t];
-      const int page = (pos >= 0 && lp < P.max_pages) ? P.page_table[(int64_t)seq * P.max_pages + lp] : -1;
-      if (page < 0 || page >= P.n_pages) {
-        set_error(P.err, 1);
-        continue;
-      }
-      const int slot = pos & 15;
-      if (head < P.hq + P.hkv) {
-        T* kp = reinterpret_cast<T*>(P.k_pool) + ((int64_t)page * P.hkv + (head - P.hq)) * PAGE * D;
-        store8(kp + k_off(slot, j0), lo);
-        store8(kp + k_off(slot, j0 + half), hi);
-      } else {
-        T* vp = reinterpret_cast<T*>(P.v_pool) + ((int64_t)page * P.hkv + (head - P.hq - P.hkv)) * PAGE * D;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          Elem<T>::store(vp, v_off(slot, j0 + i), lo[i]);
-          Elem<T>::store(vp, v_off(slot, j0 + half + i), hi[i]);
-        }
-      }
+      qkv_store<T>(P, t, head, j0, lo, hi);
     }
   } else if constexpr (EPI == EPI_SWIGLU) {
     // A thread keeps one output column (its two bias values read once) and

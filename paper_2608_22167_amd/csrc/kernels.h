@@ -252,6 +252,10 @@ hipError_t launch_gemm_tiled(int expert_fmt, const Gemm& g, hipStream_t s);
 // launch has at least two tiles per compute unit (bf16 activations, k % 32 == 0).
 bool pipe_gemm_applies(int dtype, const Gemm& g);
 hipError_t launch_gemm_pipe(int expert_fmt, const Gemm& g, hipStream_t s);
+// Direct-to-LDS rings of 64-wide slices (gemm_ring.hip): k a multiple of 64,
+// n of 16 (of 64 for the QKV projection).
+bool ring_gemm_applies(int dtype, int expert_fmt, const Gemm& g);
+hipError_t launch_gemm_ring(int expert_fmt, const Gemm& g, hipStream_t s);
 // Weight slabs (gemm_slab.hip): grouped GEMMs with bf16 activations whose
 // groups are too short for tiles (bf16 weights, under TILED_MIN_ROWS rows per
 // group) or whose MXFP4 weights dominate the traffic (up to SLAB_MAX_ROWS_FP4

@@ -1,0 +1,119 @@
+"""The direct-to-LDS ring GEMM at the edges of its tiles and of its dispatch:
+reductions shorter than the ring, half last units, partial n-tiles, rows just
+around a tile, empty and hot groups, rejected scales, both head sizes of the
+projection. Tolerances are the layer's (bf16 storage between the products)."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import oracle as O
+from paper_2608_22167_amd import mcpu, workload as W
+from tests import parity as PT
+
+pytestmark = pytest.mark.gpu
+
+
+def _shape(hidden, ffn, fmt="mxfp4", experts=8, top_k=2, **kw):
+    return replace(W.GPT_OSS_20B, hidden=hidden, ffn_dim=ffn, n_experts=experts, top_k=top_k, expert_fmt=fmt,
+                   **{**dict(n_q_heads=8, n_kv_heads=2, head_dim=64), **kw})
+
+
+def _forced_moe(s, weights, force, seed):
+    T = len(force)
+    h = W.synth_normal(seed, 5, (T, s.hidden))
+    out = torch.empty((T, s.hidden), device="cuda")
+    ws = mcpu.workspace(mcpu.moe_forward_workspace_size(s, T))
+    dw = mcpu.DeviceWeights(s, weights)
+    mcpu.moe_forward(s, dw, h.cuda(), out, None, None, torch.from_numpy(force).cuda(), ws)
+    torch.cuda.synchronize()
+    return h, out.cpu().double().numpy(), mcpu.mcpu_check_device_errors(ws)
+
+
+# rows of experts 0..: around 32-row fragments, 64- and 128-row tiles, none, and
+# one expert holding nearly all (the 40- and 512-row averages of the dispatch)
+ROWS = {"few": [1, 2, 0, 3, 1, 0, 2, 1], "tile64": [31, 32, 33, 63, 64, 0, 65, 24],
+        "tile128": [127, 128, 129, 96, 97, 0, 1, 255], "hot": [900, 0, 1, 0, 0, 5, 0, 0], "many": [700, 513, 512, 640, 515, 600, 530, 777]}
+
+
+@pytest.mark.parametrize("rows", list(ROWS))
+# 1, 3, 9 and 17 slices (half last units, the ring padded and full), n 32 .. 640 columns past whole tiles
+@pytest.mark.parametrize("hidden,ffn", [(64, 320), (192, 64), (576, 192), (1088, 128)])
+def test_mxfp4_rows_and_reductions(hidden, ffn, rows):
+    s = _shape(hidden, ffn, top_k=1)
+    wl = W.custom(s, [4], [1], 2101 + hidden)
+    force = np.random.default_rng(3).permutation(np.repeat(np.arange(8), ROWS[rows])).astype(np.int32)[:, None]
+    h, out, err = _forced_moe(s, wl.weights, force, 11)
+    assert err == 0
+    PT.check("moe out", out, O.moe(s, O.Weights(s, wl.weights), h, force_idx=force)["out"], "bf16")
+
+
+@pytest.mark.parametrize("T", [40, 400])
+def test_mxfp4_rejected_scales_contribute_nothing(T):
+    """Scales outside [2, 252], anywhere in a tile, raise the error bit, and the
+    result is that of the same weights with those blocks' codes zero."""
+    s = _shape(576, 576)
+    wl = W.custom(s, [4], [1], 2111)
+    rng = np.random.default_rng(5)
+    bad, zero = dict(wl.weights), dict(wl.weights)
+    for key in ("w_gu", "w_d"):
+        sc, codes = wl.weights[key + "_scales"].clone(), wl.weights[key + "_codes"].clone()
+        E, R, B = sc.shape
+        for v in (0, 1, 253, 254, 255):
+            for _ in range(6):
+                e, r, b = int(rng.integers(E)), int(rng.integers(R)), int(rng.integers(B))
+                sc[e, r, b] = v
+                codes[e, r, 16 * b:16 * b + 16] = 0
+        sc[0, 0, 0], sc[-1, -1, -1] = 255, 0
+        codes[0, 0, :16], codes[-1, -1, -16:] = 0, 0
+        bad[key + "_scales"], zero[key + "_codes"] = sc, codes
+    force = rng.integers(0, 8, size=(T, 2)).astype(np.int32)
+    _, want, err0 = _forced_moe(s, zero, force, 12)
+    _, got, err = _forced_moe(s, bad, force, 12)
+    assert err0 == 0 and err & mcpu.DEVERR_MXFP4
+    # a rejected block weighs 6 x 2^-125 at most: far below one ulp of any sum here
+    np.testing.assert_allclose(got, want, rtol=0, atol=1e-30)
+
+
+@pytest.mark.parametrize("pack", [False, True])
+@pytest.mark.parametrize("ffn", [576, 192])
+def test_bf16_experts(pack, ffn):
+    """bf16 groups of 48 to 255 rows on average, row-major and streaming-order weights."""
+    s = _shape(576, ffn, fmt="dense", top_k=1)
+    wl = W.custom(s, [4], [1], 2121)
+    rows = [127, 128, 129, 0, 1, 33, 255, 64]
+    force = np.random.default_rng(3).permutation(np.repeat(np.arange(8), rows)).astype(np.int32)[:, None]
+    T = len(force)
+    h = W.synth_normal(13, 5, (T, s.hidden))
+    out = torch.empty((T, s.hidden), device="cuda")
+    ws = mcpu.workspace(mcpu.moe_forward_workspace_size(s, T))
+    mcpu.moe_forward(s, mcpu.DeviceWeights(s, wl.weights, pack=pack), h.cuda(), out, None, None,
+                     torch.from_numpy(force).cuda(), ws)
+    torch.cuda.synchronize()
+    assert mcpu.mcpu_check_device_errors(ws) == 0
+    PT.check("moe out", out.cpu().double().numpy(), O.moe(s, O.Weights(s, wl.weights), h, force_idx=force)["out"], "bf16")
+
+
+# 128 x 128 tiles above the dispatch's bound for both projections: 64-wide heads
+# with a ragged last m-tile, and 32-wide ones (two heads a piece, a partial last n-tile)
+@pytest.mark.parametrize("pack", [False, True])
+@pytest.mark.parametrize("kw,T", [(dict(hidden=2112, n_q_heads=64, n_kv_heads=8, head_dim=64), 2300),
+                                  (dict(hidden=2112, n_q_heads=60, n_kv_heads=6, head_dim=32), 2700)])
+def test_projections(kw, T, pack):
+    s = _shape(ffn=64, **kw)
+    rng = np.random.default_rng(2131)
+    wl = W.custom(s, rng.integers(1, 60, size=T), np.ones(T), 2131)
+    step = mcpu.DeviceStep(wl)
+    step.weights = mcpu.DeviceWeights(s, wl.weights, pack=pack)
+    q = torch.empty((T, s.n_q_heads, s.head_dim), dtype=torch.bfloat16, device="cuda")
+    o = torch.empty((T, s.attn_dim), dtype=torch.bfloat16, device="cuda")
+    h1 = torch.empty((T, s.hidden), device="cuda")
+    step.run(mcpu.Taps(q=q.data_ptr(), o=o.data_ptr(), h1=h1.data_ptr()))
+    torch.cuda.synchronize()
+    assert step.device_errors() == 0
+    seqs = sorted({0, 127, 128, T - 1, T - 2} | {int(b) for b in rng.choice(T, 6, replace=False)})
+    sub, rows = W.restrict(wl, seqs)
+    ref = O.decode_layer(sub)
+    for name, got in (("q", q), ("o", o), ("h1", h1)):
+        PT.check(name, got[torch.from_numpy(rows).cuda()].float().cpu().double().numpy().reshape(ref[name].shape), ref[name], "bf16")
