@@ -15,6 +15,8 @@
 // because the score tile's lane layout is exactly the value product's B
 // operand layout. The page format (include/mcpu.h) makes every K and V
 // fragment load a contiguous 512 B - 1 KiB segment per wavefront.
+#include <type_traits>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -825,13 +827,358 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefill P) {
   }
 }
 
+// bf16, head dim 64: the same split of the work, on 32 x 32 x 16 products. Per
+// step (two pages, 32 keys) a wavefront forms S^T = K Q^T as one 32 x 32 tile
+// per 32 columns and O^T += V^T P^T from it. A product of this size keeps the
+// matrix cores busy for 32 cycles and the vector pipe for one issue slot, so
+// the softmax of one wavefront runs beside the products of the other on its
+// SIMD (and beside its own: the scores of step s + 1 are formed ahead of the
+// softmax of step s); the 16 x 16 tiles of the kernel above block the pipe
+// twice as often and need four cross-lane maxima where this needs two.
+//
+// Lane l of a score tile holds column l % 32 and, with h = l / 32, the keys
+// 8 q + 4 h + r (q, r < 4; element 4 q + r). The value product of page p takes
+// its eight k-slots 4 (q % 2) + r straight from elements q / 2 == p, and its
+// other operand, the value rows 8 (q % 2) + 4 h + r of one dim, is two 8-byte
+// pieces of the page format 256 bytes apart: one two-address LDS read. Row
+// sums are dot products of the packed weights with ones.
+//
+// Pages go straight to LDS (wavefront 0: K of the first page, 1: of the second,
+// 2 and 3: their V) through PRS stages; the 16-byte pieces of V are permuted
+// on the way (128-byte block b of a 512-byte dim tile to b ^ (tile & 1)) so
+// that the lanes of a half tile read all banks.
+//
+// The maximum of a column is raised only when a lane's share of a step's
+// weights would pass 2^40 (WEIGHT_LIMIT): below that, sums and accumulators stay far inside fp32
+// and a bf16 weight's relative error does not depend on its exponent, so the
+// rescale of the accumulators is rare instead of per step.
+//
+// Bound: the vector pipe, about 126 instructions per wavefront and step (the 64
+// x 32 exponentials cost two slots each). Measured against the 16 x 16 tiles,
+// 64 query heads on 8 KV heads: twelve chunks (32 K tokens) behind up
+// to 24 K keys 10.36 -> 8.27 ms, six chunks (1.8 K tokens) behind up to 16 K
+// 383 -> 273 us.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) void* lds_void_t;
+constexpr int PRS = 6;  // LDS stages of two pages' K and V (8 KB)
+
+template <int G>
+__global__ __launch_bounds__(256) void attn_prefill_wide_kernel(AttnPrefill P) {
+  using SH = PrefillShape<G>;
+  constexpr int D = 64, PE = PAGE * D, PB = 2 * PE;  // page elements and bytes of one KV head
+  __shared__ __align__(1024) uint8_t s0[4 * PB];
+  __shared__ __align__(1024) uint8_t s1[4 * PB];
+  __shared__ __align__(1024) uint8_t s2[4 * PB];
+  __shared__ __align__(1024) uint8_t s3[4 * PB];
+  __shared__ __align__(1024) uint8_t s4[4 * PB];
+  __shared__ __align__(1024) uint8_t s5[4 * PB];
+  auto stage_of = [&](int s) __attribute__((always_inline)) {
+    return s == 0 ? s0 : s == 1 ? s1 : s == 2 ? s2 : s == 3 ? s3 : s == 4 ? s4 : s5;
+  };
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  const int g = blockIdx.x % P.hkv;
+  const int blk = P.n_blocks - 1 - (int)(blockIdx.x / P.hkv);  // latest (heaviest) blocks first
+  int lo_b = 0, hi_b = P.batch - 1;                            // sequence: last b with blk_start[b] <= blk
+  while (lo_b < hi_b) {
+    const int mid = (lo_b + hi_b + 1) >> 1;
+    if (P.blk_start[mid] <= blk) lo_b = mid; else hi_b = mid - 1;
+  }
+  const int b = uniform(lo_b);
+  const int q0 = P.cu_q[b], q1 = P.cu_q[b + 1];
+  const int t0 = uniform(q0 + (blk - P.blk_start[b]) * SH::QB);
+  const int ntok = min(SH::QB, q1 - t0);
+  const int p_first = uniform(P.seq_lens[b] + (t0 - q0)), p_last = p_first + ntok - 1;
+  const int lo = P.window > 0 ? max(0, p_first - P.window + 1) : 0;
+  const int pg_lo = lo / PAGE, pg_last = p_last / PAGE;
+  int n_steps = uniform((pg_last - pg_lo + 2) / 2);
+  if (ntok <= 0 || p_first < 0 || pg_last >= P.max_pages) {
+    if (tid == 0) set_error(P.err, 1);
+    n_steps = 0;
+  }
+  const int32_t* ptab = P.page_table + (int64_t)b * P.max_pages;
+
+  // this lane's column in each of the wavefront's two 32-column tiles
+  const int fc = lane & 31, h = lane >> 5;
+  int pos[2], head[2];
+  bool valid[2];
+  Frag<bf16> qf[2][4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int c = 32 * j + fc, ti = wave * SH::TPW + c / G;
+    valid[j] = ti < ntok;
+    pos[j] = p_first + ti;
+    head[j] = g * G + c % G;
+    const int trow = min(max(t0 + ti, 0), P.n_tokens - 1);  // in range even if the tables disagree
+    const bf16* qp = reinterpret_cast<const bf16*>(P.q) + ((int64_t)trow * P.hq + head[j]) * D + 8 * h;
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc) {
+      qf[j][cc].load(qp + 16 * cc);
+      qf[j][cc].keep_if(valid[j]);
+    }
+  }
+
+  // page ids of steps base .. base + 31, lane i: page pg_lo + 2 base + i (the
+  // last page past the range). A block of IDB steps and the requests ahead of it
+  // find their ids in one register; the next block's are loaded a block ahead.
+  constexpr int IDB = 4 * PRS;
+  static_assert(IDB + PRS - 1 <= 32, "a block's ids and those requested ahead of it");
+  auto ids_of = [&](int base) __attribute__((always_inline)) {
+    return n_steps > 0 ? ptab[min(pg_lo + 2 * base + lane, pg_last)] : 0;
+  };
+  int ids = ids_of(0), base = 0;
+  const int step_bytes = P.hkv * PB;  // bytes of a page in one pool (below 2^31: hkv * 2 KB)
+  const uint8_t* pool = reinterpret_cast<const uint8_t*>(wave < 2 ? P.k_pool : P.v_pool) + (int64_t)g * PB;
+  // the wavefront's piece of a step: 2 KB, lane l of load u at byte 1024 u + 16 l
+  uint32_t vo[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const uint32_t at = 1024u * u + 16u * lane;
+    vo[u] = wave < 2 ? at : at ^ (((at >> 9) & 1u) << 7);
+  }
+  // a page's id, or 0 with good = false where the table has none
+  auto page_of = [&](int step, int which, bool& good) __attribute__((always_inline)) {
+    const int id = __builtin_amdgcn_readlane(ids, 2 * (step - base) + which);
+    good = id >= 0 && id < P.n_pages;
+    return good ? id : 0;
+  };
+  // request a step's pages (past the end: the last page again, not used)
+  auto request = [&](uint8_t* stg, int step) __attribute__((always_inline)) {
+    bool good;
+    const int id = page_of(step, wave & 1, good);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(pool) + (int64_t)id * step_bytes, 0, PB, 0x00020000);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t)(stg + wave * PB + 1024 * u), 16, vo[u], 0, 0, 0);
+  };
+
+  constexpr float WEIGHT_LIMIT = 0x1p40f;  // of a lane's 16 weights in a step
+  float m_run[2], m_sub[2], limit[2], l[2];  // limit: -inf until a key is visible
+  f32x16 acc[2][2];  // [dim tile][column tile]
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    m_run[j] = -INFINITY;
+    m_sub[j] = 0.f;
+    limit[j] = -INFINITY;
+    l[j] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[dt][j][e] = 0.f;
+  }
+  const int pos_lo_w = p_first + wave * SH::TPW;
+  const int pos_hi_w = min(pos_lo_w + SH::TPW - 1, p_last);
+  // fragment addresses: key fc of the step (page fc / 16), dims 8 h .. of a
+  // 16-dim chunk; dim fc of a tile of 32, value rows 4 h .. and 8 + 4 h ..
+  const uint32_t ko = (fc >> 4) * PB + ((h * 16 + (fc & 15)) * 16);
+  const uint32_t vbase = (fc >> 4) * 512 + (fc & 15) * 8 + (((uint32_t)h ^ ((fc >> 4) & 1)) << 7);
+
+  struct Scores {
+    f32x16 t[2];
+  };
+  auto load_keys = [&](u32x4_t (&kf)[4], const uint8_t* stg) __attribute__((always_inline)) {
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc) kf[cc] = *reinterpret_cast<const u32x4_t*>(stg + ko + 512 * cc);
+  };
+  auto scores = [&](Scores& sc, const u32x4_t (&kf)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sc.t[j][e] = 0.f;
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        sc.t[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kf[cc]),
+                                                          __builtin_bit_cast(bf16x8_t, qf[j][cc].v), sc.t[j], 0, 0, 0);
+  };
+  // step's softmax and value products from its scores, and the scores of the next step
+  auto attend = [&](Scores& sc, Scores& sn, const uint8_t* stg, const uint8_t* nxt, int step) __attribute__((always_inline)) {
+    u32x4_t kf[4];
+    load_keys(kf, nxt);
+    bool ok[2];
+    page_of(step, 0, ok[0]);
+    page_of(step, 1, ok[1]);
+    const int pg0 = pg_lo + 2 * step, k0 = pg0 * PAGE;
+    const bool edge = k0 + 2 * PAGE - 1 > pos_lo_w || (P.window > 0 && k0 < pos_hi_w - P.window + 1) ||
+                      !ok[0] || !ok[1] || pg0 + 1 > pg_last;
+    if (__builtin_expect(edge, 0)) {  // wave-uniform; the empty asm keeps it a branch
+      asm volatile("");
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int hi = pos[j], lo_c = P.window > 0 ? pos[j] - P.window + 1 : 0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int kp = k0 + 8 * (e >> 2) + 4 * h + (e & 3), pg = e >> 3;
+          const bool in = ok[pg] && pg0 + pg <= pg_last && kp >= lo_c && kp <= hi;
+          sc.t[j][e] = in ? sc.t[j][e] : -INFINITY;
+        }
+      }
+    }
+    u32x4_t pw[2][2];  // [column tile][page]: the weights, packed
+    float sum[2];
+    auto weights = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        sum[j] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc.t[j][e], P.scale_log2, -m_sub[j]));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(sc.t[j][e + 1], P.scale_log2, -m_sub[j]));
+          const uint32_t w = pack_bf16(p0, p1);
+          pw[j][e >> 3][(e & 7) >> 1] = w;
+          sum[j] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w), __builtin_bit_cast(bf16x2_t, 0x3F803F80u), sum[j], false);
+        }
+      }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    scores(sn, kf);
+    weights();
+    // the next scores' eight products among the 96 vector instructions of the weights
+#define PF_MIX                                        \
+  __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  \
+  __builtin_amdgcn_sched_group_barrier(0x402, 12, 0);
+    PF_MIX PF_MIX PF_MIX PF_MIX PF_MIX PF_MIX PF_MIX PF_MIX
+#undef PF_MIX
+    // The maximum only has to keep the weights in range (bf16 and fp32 are
+    // relative), so it is raised when a step's sum says that they are not, and
+    // until a column has seen a key; the weights are then formed again.
+    const bool raise = sum[0] > limit[0] || sum[1] > limit[1];
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {  // wave-uniform (kept a branch)
+      asm volatile("");
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        float mloc = sc.t[j][0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e) mloc = vmax(mloc, sc.t[j][e]);
+        const uint32_t u = __float_as_uint(mloc);
+        auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        const float mstep = vmax(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * P.scale_log2;
+        const float m_new = fmaxf(m_run[j], mstep);
+        const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m_run[j] - m_new);
+        l[j] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt) acc[dt][j] *= alpha;
+        m_run[j] = m_new;
+        m_sub[j] = m_new == -INFINITY ? 0.f : m_new;  // masked scores give 2^-inf = 0
+        limit[j] = m_new == -INFINITY ? -INFINITY : WEIGHT_LIMIT;
+      }
+      weights();
+    }
+    u32x4_t vf[2][2];  // [page][dim tile]
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt) {
+        const uint8_t* v = stg + (2 + pg) * PB + 1024 * dt + vbase;
+        const u32x2_t a = *reinterpret_cast<const u32x2_t*>(v), c = *reinterpret_cast<const u32x2_t*>(v + 256);
+        vf[pg][dt] = __builtin_shufflevector(a, c, 0, 1, 2, 3);
+      }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      l[j] += sum[j];
+#pragma unroll
+      for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+          acc[dt][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, vf[pg][dt]),
+                                                               __builtin_bit_cast(bf16x8_t, pw[j][pg]), acc[dt][j], 0, 0, 0);
+    }
+  };
+
+  // Step s sits in stage s % PRS. In step s its scores are there already; step
+  // s + PRS - 1 is requested into the stage step s - 1 left, the scores of step
+  // s + 1 are formed, and before the barrier a wavefront waits for its loads of
+  // step s + 2.
+  if (n_steps > 0) {
+    auto publish = [&]() __attribute__((always_inline)) {
+      constexpr int N = 2 * (PRS - 3);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(N | (7 << 4) | (15 << 8));  // vmcnt(N) expcnt(7) lgkmcnt(15)
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int s = 0; s < PRS - 1; ++s) {
+      request(stage_of(s), s);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    publish();
+    Scores sc[2];
+    {
+      u32x4_t kf[4];
+      load_keys(kf, s0);
+      scores(sc[0], kf);
+    }
+    auto one = [&](auto U_, int step) __attribute__((always_inline)) {
+      constexpr int U = decltype(U_)::value;
+      if (step < n_steps) {  // uniform
+        request(stage_of((U + PRS - 1) % PRS), step + PRS - 1);
+        attend(sc[U % 2], sc[(U + 1) % 2], stage_of(U), stage_of((U + 1) % PRS), step);
+      }
+      publish();
+    };
+    while (true) {
+      const int ids_next = ids_of(base + IDB), stop = min(n_steps, base + IDB);
+      for (int step = base; step < stop; step += PRS) {
+        one(std::integral_constant<int, 0>{}, step);
+        one(std::integral_constant<int, 1>{}, step + 1);
+        one(std::integral_constant<int, 2>{}, step + 2);
+        one(std::integral_constant<int, 3>{}, step + 3);
+        one(std::integral_constant<int, 4>{}, step + 4);
+        one(std::integral_constant<int, 5>{}, step + 5);
+      }
+      if (stop == n_steps) break;
+      base = stop;
+      ids = ids_next;
+    }
+  }
+  __builtin_amdgcn_s_waitcnt(0);  // no load into LDS may outlive the workgroup
+
+  // normalise with the sink and store this lane's dims 32 dt + 8 q + 4 h .. + 3 of each column
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const uint32_t u = __float_as_uint(l[j]);
+    auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    float l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    float M = m_run[j], scale = 1.0f;
+    if (P.sinks) {
+      const float sk = P.sinks[head[j]] * LOG2E;
+      const float Mt = fmaxf(M, sk);
+      const float f = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - Mt);
+      l_tot = l_tot * f + __builtin_amdgcn_exp2f(sk - Mt);
+      scale = f;
+    }
+    const float inv = l_tot > 0.f ? scale / l_tot : 0.f;
+    if (valid[j]) {
+      bf16* o = reinterpret_cast<bf16*>(P.o) + ((int64_t)(t0 + wave * SH::TPW + (32 * j + fc) / G) * P.hq + head[j]) * D + 4 * h;
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          store4(o + 32 * dt + 8 * q, make_float4(acc[dt][j][4 * q] * inv, acc[dt][j][4 * q + 1] * inv,
+                                                  acc[dt][j][4 * q + 2] * inv, acc[dt][j][4 * q + 3] * inv));
+    }
+  }
+}
+
 template <typename T, int D>
 static hipError_t prefill_impl(int group, const AttnPrefill& p, hipStream_t s) {
   dim3 grid((unsigned)(p.n_blocks * p.hkv)), block(256);
-  switch (group) {
-    case 4: hipLaunchKernelGGL((attn_prefill_kernel<T, D, 4>), grid, block, 0, s, p); break;
-    case 8: hipLaunchKernelGGL((attn_prefill_kernel<T, D, 8>), grid, block, 0, s, p); break;
-    default: return hipErrorInvalidValue;
+  // bf16 with head dim 64 takes the wide products (figures at the kernel);
+  // float has no such tile, and only the smallest configuration has head dim 32.
+  if constexpr (sizeof(T) == 2 && D == 64) {
+    switch (group) {
+      case 4: hipLaunchKernelGGL(attn_prefill_wide_kernel<4>, grid, block, 0, s, p); break;
+      case 8: hipLaunchKernelGGL(attn_prefill_wide_kernel<8>, grid, block, 0, s, p); break;
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (group) {
+      case 4: hipLaunchKernelGGL((attn_prefill_kernel<T, D, 4>), grid, block, 0, s, p); break;
+      case 8: hipLaunchKernelGGL((attn_prefill_kernel<T, D, 8>), grid, block, 0, s, p); break;
+      default: return hipErrorInvalidValue;
+    }
   }
   return hipGetLastError();
 }

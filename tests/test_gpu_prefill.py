@@ -171,3 +171,44 @@ def test_mixed_step_full_size_longest_chunk_sampled():
         force[local[tie]] = g["idx"][tie]
         ref = O.decode_layer(sub, rows=local, force_idx=force)
     compare_layer(sub, g, None, ref)
+
+
+@pytest.mark.parametrize("scale", [1.0, 40.0, -40.0])
+@pytest.mark.parametrize("window", [0, 128])
+@pytest.mark.parametrize("hq,hkv", [(16, 2), (8, 2)])
+def test_prefill_score_range(hq, hkv, window, scale):
+    """Chunks whose scores climb (or fall) along the context, at scale 40 by
+    thousands of powers of two: the running maximum starts at a column's first
+    visible key, is raised when weights leave the range, and earlier weights
+    vanish. Chunks shorter than a block, past one, and behind 0, 13, 500 and
+    2000 cached keys (more than one block of page ids); with and without sinks.
+    Scores are large, so the softmax is nearly one-hot: bf16 storage of q, k, v,
+    the weights and o bounds the difference."""
+    s = replace(W.GPT_OSS_20B, hidden=256, n_q_heads=hq, n_kv_heads=hkv, window=window)
+    wl = W.custom(s, [0, 13, 500, 2000], [17, 70, 33, 40], 1190, weights=False)
+    rng = np.random.default_rng(7)
+    T = wl.n_tokens
+    q = torch.from_numpy(rng.standard_normal((T, hq, 64)).astype(np.float32))
+    # a common direction in q and k whose weight grows with the position
+    d = torch.from_numpy(rng.standard_normal(64).astype(np.float32))
+    q = (q + d * scale).to(torch.bfloat16)
+    k = wl.k_pool.float()
+    for b in range(wl.batch):
+        for lp, page in enumerate(wl.page_table[b]):
+            if page >= 0:  # [hkv, 16, 64] in page order; dims run in blocks of 8: [8][16][8]
+                k[page] += (lp / 20.0) * d.view(8, 1, 8).expand(8, 16, 8).reshape(1, 16, 64)
+    k = k.to(torch.bfloat16)
+    for sinks in (None, torch.linspace(-3, 3, hq)):
+        o = torch.empty((T, hq * 64), dtype=torch.bfloat16, device="cuda")
+        kd, vd = k.cuda(), wl.v_pool.cuda()
+        ws = mcpu.workspace(mcpu.paged_attention_workspace_size(s, wl.batch, T))
+        mcpu.paged_attention(s, None if sinks is None else sinks.cuda(), mcpu.KVPool(s, kd, vd),
+                             torch.from_numpy(wl.page_table).cuda(), torch.from_numpy(wl.seq_lens).cuda(),
+                             torch.from_numpy(wl.cu_q).cuda(), wl.seq_lens, wl.cu_q, q.cuda(), o, ws)
+        torch.cuda.synchronize()
+        assert mcpu.mcpu_check_device_errors(ws) == 0
+        seq = np.repeat(np.arange(wl.batch), wl.q_lens)
+        pos = np.concatenate([np.arange(l, l + n) for l, n in zip(wl.seq_lens, wl.q_lens)])
+        ref = O.attention(s, seq, pos, q.double().numpy(), k.float().numpy(), wl.v_pool.float().numpy(), wl.page_table,
+                          None if sinks is None else sinks.numpy())
+        PT.check("o", o.float().cpu().double().numpy().reshape(ref.shape), ref, "bf16")
