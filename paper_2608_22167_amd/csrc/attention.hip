@@ -7,14 +7,15 @@
 //   split   one wavefront per (split, KV head) streams the split's K and V
 //           pages and keeps a running max / sum / weighted value sum for the
 //           G = Hq / Hkv query heads that share the KV head;
-//   combine one workgroup per token merges the splits and adds the sink to
-//           the normaliser.
+//   combine a wavefront per (token, query head) merges the splits and adds the
+//           sink to the normaliser.
 // The score and value products run on the matrix cores: with keys as rows
 // and the G query heads as columns (padded to 16), S^T = K q^T is one 16x16
 // tile per page, and O^T += V^T P^T consumes it without any lane shuffle
 // because the score tile's lane layout is exactly the value product's B
 // operand layout. The page format (include/mcpu.h) makes every K and V
 // fragment load a contiguous 512 B - 1 KiB segment per wavefront.
+#include <algorithm>
 #include <type_traits>
 
 #include "device.h"
@@ -68,6 +69,85 @@ __device__ int block_exclusive_scan(int local, int* sums, int& total) {
   return excl;
 }
 
+constexpr int PLAN_SEQS = 2048;  // cu_q of up to this many sequences is searched in LDS
+constexpr int PLAN_TILE = 4;     // from this many tiles of one token per thread on, four per thread
+
+// The token part of the plan by one workgroup, in tiles of V consecutive tokens
+// per thread: positions, the running split count, and the splits' descriptors,
+// which a wavefront writes together (lane j the tile's j-th split), because a
+// few tokens with long contexts have many splits each. Returns their number.
+// One tile costs a scan of the workgroup (three barriers), so many tokens take
+// four per thread; with few, one per thread spreads the descriptors over more
+// wavefronts. Bound by latency. Against a contiguous run of tokens per thread with a
+// search in memory and a serial loop over descriptors: one token with 16 K keys
+// 10.5 -> 5.5 us, 31 K tokens 184 -> 164 us (the norm beside it moves 540 MB).
+template <int V>
+__device__ int plan_tokens(const AttnPlan& P, const int32_t* cu, int* sums) {
+  const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x;
+  int base = 0;
+  for (int tile = 0; tile < P.n_tokens; tile += V * nt) {
+    const int t0 = tile + V * tid;
+    int seq[V], pos[V], ns[V], local = 0;
+    int b = cu ? seq_of_token(cu, P.batch, min(t0, P.n_tokens - 1)) : 0;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const int t = t0 + i;
+      seq[i] = pos[i] = ns[i] = 0;
+      if (t >= P.n_tokens) continue;
+      if (cu) {
+        while (b < P.batch - 1 && cu[b + 1] <= t) ++b;
+      } else {
+        b = t;
+      }
+      seq[i] = b;
+      pos[i] = P.seq_lens[b] + (cu ? t - cu[b] : 0);
+      const bool pre = cu && P.prefill_min_q > 0 && cu[b + 1] - cu[b] >= P.prefill_min_q;
+      ns[i] = pre ? 0 : token_splits(pos[i], P.window, P.pps);
+      local += ns[i];
+    }
+    int total = 0;
+    int run = base + block_exclusive_scan(local, sums, total);
+    int start[V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      start[i] = run;
+      run += ns[i];
+      if (t0 + i < P.n_tokens) {
+        P.tok_seq[t0 + i] = seq[i];
+        P.tok_pos[t0 + i] = pos[i];
+        P.split_start[t0 + i] = start[i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const int n = max(ns[i], 0);
+      const int incl = wave_incl_scan(n);
+      const int all = __shfl(incl, 63, 64);
+      for (int j0 = 0; j0 < all; j0 += 64) {
+        const int j = j0 + lane;
+        int o = 0;  // the first lane with incl > j: the token of split j
+#pragma unroll
+        for (int step = 32; step; step >>= 1) o += __shfl(incl, o + step - 1, 64) <= j ? step : 0;
+        const int src = min(o, 63);
+        const int k = j - (__shfl(incl, src, 64) - __shfl(n, src, 64)), ns_o = __shfl(n, src, 64);
+        const int at = __shfl(start[i], src, 64) + k, p = __shfl(pos[i], src, 64), sq = __shfl(seq[i], src, 64);
+        if (j >= all || (unsigned)at >= (unsigned)max(P.host_total_splits, 0)) continue;
+        // the token's splits share its np pages evenly (sizes differ by at most one)
+        const int lo = P.window > 0 ? max(0, p - P.window + 1) : 0;
+        const int first = lo / PAGE, np = p / PAGE - first + 1;
+        SplitDesc d;
+        d.t = tile + V * (tid - lane + src) + i; d.b = sq; d.p = p; d.lo = lo;
+        d.pg0 = first + (int)((int64_t)k * np / ns_o);
+        d.pg1 = first + (int)((int64_t)(k + 1) * np / ns_o);
+        d.pad0 = d.pad1 = 0;
+        P.split_desc[at] = d;
+      }
+    }
+    base += total;
+  }
+  return base;
+}
+
 // Workgroups 1.. of the plan launch: the layer's first RMSNorm, y = x /
 // sqrt(mean(x^2) + eps) * g, on four rows per workgroup (256 threads a row,
 // float4 j of a thread at features 4 (t + 256 j)), so that the norm and the
@@ -114,39 +194,18 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(AttnPlan P) {
     return;
   }
   __shared__ int sums[160];
+  __shared__ int cu_s[PLAN_SEQS + 1];
   const int tid = threadIdx.x, nt = blockDim.x;
   for (int i = tid; i < P.n_zero; i += nt) P.zero[i] = 0;
-  // tokens: positions and split counts (no splits for prefill sequences)
-  const int per = (P.n_tokens + nt - 1) / nt;
-  const int t0 = min(P.n_tokens, tid * per), t1 = min(P.n_tokens, t0 + per);
-  int local = 0;
-  for (int t = t0; t < t1; ++t) {
-    int b = P.cu_q ? seq_of_token(P.cu_q, P.batch, t) : t;
-    int pos = P.seq_lens[b] + (P.cu_q ? t - P.cu_q[b] : 0);
-    local += is_prefill(P, b) ? 0 : token_splits(pos, P.window, P.pps);
+  const int32_t* cu = P.cu_q;
+  if (cu && P.batch <= PLAN_SEQS) {
+    for (int i = tid; i <= P.batch; i += nt) cu_s[i] = cu[i];
+    __syncthreads();
+    cu = cu_s;
   }
   int total = 0;
-  int run = block_exclusive_scan(local, sums, total);
-  for (int t = t0; t < t1; ++t) {
-    int b = P.cu_q ? seq_of_token(P.cu_q, P.batch, t) : t;
-    int pos = P.seq_lens[b] + (P.cu_q ? t - P.cu_q[b] : 0);
-    P.tok_seq[t] = b;
-    P.tok_pos[t] = pos;
-    P.split_start[t] = run;
-    const int ns = is_prefill(P, b) ? 0 : token_splits(pos, P.window, P.pps);
-    // the token's ns splits share its np pages evenly (sizes differ by at most one)
-    const int lo = P.window > 0 ? max(0, pos - P.window + 1) : 0;
-    const int first = lo / PAGE, np = pos / PAGE - first + 1;
-    for (int k = 0; k < ns && run + k < P.host_total_splits; ++k) {
-      SplitDesc d;
-      d.t = t; d.b = b; d.p = pos; d.lo = lo;
-      d.pg0 = first + (int)((int64_t)k * np / ns);
-      d.pg1 = first + (int)((int64_t)(k + 1) * np / ns);
-      d.pad0 = d.pad1 = 0;
-      P.split_desc[run + k] = d;
-    }
-    run += ns;
-  }
+  if (P.n_tokens <= PLAN_TILE * nt) total = plan_tokens<1>(P, cu, sums);
+  else total = plan_tokens<4>(P, cu, sums);
   if (tid == 0) {
     P.split_start[P.n_tokens] = total;
     if (P.host_total_splits >= 0 && total != P.host_total_splits) set_error(P.err, 8);
@@ -155,10 +214,10 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(AttnPlan P) {
   // sequences: prefill blocks of prefill_qb tokens
   const int perb = (P.batch + nt - 1) / nt;
   const int b0 = min(P.batch, tid * perb), b1 = min(P.batch, b0 + perb);
-  local = 0;
+  int local = 0;
   for (int b = b0; b < b1; ++b)
     if (is_prefill(P, b)) local += (P.cu_q[b + 1] - P.cu_q[b] + P.prefill_qb - 1) / P.prefill_qb;
-  run = block_exclusive_scan(local, sums, total);
+  int run = block_exclusive_scan(local, sums, total);
   for (int b = b0; b < b1; ++b) {
     P.blk_start[b] = run;
     if (is_prefill(P, b)) run += (P.cu_q[b + 1] - P.cu_q[b] + P.prefill_qb - 1) / P.prefill_qb;
@@ -465,75 +524,103 @@ hipError_t launch_attn_split(int dtype, int head_dim, const AttnSplit& p, hipStr
 // combine: o_h = sum_s 2^{m_s - M} acc_s / (2^{sink_h log2e - M} + sum_s 2^{m_s - M} l_s)
 // ---------------------------------------------------------------------------
 
-// One wavefront per (token, query head); lane i owns dim i. The splits are
-// merged in order with a running maximum, so one pass reads each partial once.
+// A wavefront merges the splits of one query head of K tokens, n_waves / hq
+// apart (1 up to COMBINE_WAVES wavefronts): in a step that also prefills most
+// tokens have no splits, and one look at K tokens' split ranges skips them all
+// (31 K tokens with 48 decoding: 133 -> 10.7 us against a wavefront per token and
+// head; bound by their launches).
+// Per 64 splits, lane j holds split j's maximum and sum; the partial rows are
+// read four dims per lane, 256 / D rows per load and eight loads at a time, so
+// that one token with many splits waits for few round trips (16 K keys: 11.1 ->
+// 4.6 us against four rows in order at a time).
+constexpr int COMBINE_WAVES = 65536;
+
 template <typename T, int D>
-__global__ __launch_bounds__(256) void attn_combine_kernel(AttnCombine P) {
+__global__ __launch_bounds__(256) void attn_combine_kernel(AttnCombine P, int stride, int K) {
+  constexpr int LR = D / 4, RW = 64 / LR, U = 8;  // lanes per row, rows per load, loads in flight
   const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = lane_id();
-  if (item >= P.n_tokens * P.hq) return;
-  const int t = uniform(item / P.hq), h = uniform(item - (item / P.hq) * P.hq);
-  const int s0 = min(uniform(P.split_start[t]), P.n_splits);
-  const int s1 = min(uniform(P.split_start[t + 1]), P.n_splits);
-  if (s0 == s1) return;  // a prefill token: its row comes from the prefill kernel
-  float M = P.sinks ? P.sinks[h] * LOG2E : -INFINITY;
-  float L = P.sinks ? 1.0f : 0.0f;  // the sink's own term, 2^(sink - M)
-  float a = 0.f;
-  const bool act = lane < D;
-  constexpr int U = 4;
-  int s = s0;
-  for (; s + U <= s1; s += U) {
-    float m[U], l[U], v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t row = (int64_t)(s + u) * P.hq + h;
-      m[u] = P.part_ml[row * 2];
-      l[u] = P.part_ml[row * 2 + 1];
-      v[u] = act ? P.part_acc[row * D + lane] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (m[u] == -INFINITY) continue;  // a split whose pages were all missing
-      if (m[u] > M) {
-        const float r = __builtin_amdgcn_exp2f(M - m[u]);
-        L *= r;
-        a *= r;
-        M = m[u];
+  const int lane = lane_id(), sub = lane / LR, dim = 4 * (lane % LR);
+  if (item >= stride * P.hq) return;
+  const int tb = uniform(item / P.hq), h = uniform(item - (item / P.hq) * P.hq);
+  int b0 = 0, b1 = 0;  // lane k: the split range of token tb + k * stride
+  if (lane < K && tb + lane * stride < P.n_tokens) {
+    b0 = min(P.split_start[tb + lane * stride], P.n_splits);
+    b1 = min(P.split_start[tb + lane * stride + 1], P.n_splits);
+  }
+  // tokens without splits are prefill tokens: their rows come from the prefill kernel
+  for (uint64_t todo = __ballot(b0 < b1); todo; todo &= todo - 1) {
+    const int k = __builtin_ctzll(todo);
+    const int s0 = __builtin_amdgcn_readlane(b0, k), s1 = __builtin_amdgcn_readlane(b1, k);
+    float M = P.sinks ? P.sinks[h] * LOG2E : -INFINITY;
+    float L = P.sinks && lane == 0 ? 1.0f : 0.0f;  // the sink's own term, 2^(sink - M); summed over lanes at the end
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int base = s0; base < s1; base += 64) {
+      const int n = min(64, s1 - base);
+      float m = -INFINITY, l = 0.f;
+      if (lane < n) {
+        const float2 ml = *reinterpret_cast<const float2*>(P.part_ml + ((int64_t)(base + lane) * P.hq + h) * 2);
+        m = ml.x;
+        l = ml.y;
       }
-      const float f = __builtin_amdgcn_exp2f(m[u] - M);
-      L += f * l[u];
-      a += f * v[u];
+      const float Mn = fmaxf(M, wave_max(m));
+      const bool missing = m == -INFINITY;  // a split whose pages were all missing: its row is not read
+      float f = 0.f;
+      if (Mn != -INFINITY) {
+        const float r = __builtin_amdgcn_exp2f(M - Mn);
+        L *= r;
+        a.x *= r; a.y *= r; a.z *= r; a.w *= r;
+        M = Mn;
+        f = __builtin_amdgcn_exp2f(m - Mn);
+        if (!missing) L += f * l;
+      }
+      const float fx = missing ? -1.0f : f;
+      for (int j = 0; j < n; j += U * RW) {
+        float4 v[U];
+        float w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int row = j + u * RW + sub;
+          w[u] = __shfl(fx, row & 63, 64);
+          const bool use = row < n && w[u] != -1.0f;
+          w[u] = use ? w[u] : 0.f;
+          v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (use) v[u] = *reinterpret_cast<const float4*>(P.part_acc + ((int64_t)(base + row) * P.hq + h) * D + dim);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          a.x += w[u] * v[u].x; a.y += w[u] * v[u].y; a.z += w[u] * v[u].z; a.w += w[u] * v[u].w;
+        }
+      }
     }
-  }
-  for (; s < s1; ++s) {
-    const int64_t row = (int64_t)s * P.hq + h;
-    const float m = P.part_ml[row * 2];
-    if (m == -INFINITY) continue;
-    if (m > M) {
-      const float r = __builtin_amdgcn_exp2f(M - m);
-      L *= r;
-      a *= r;
-      M = m;
+    L = wave_sum(L);
+#pragma unroll
+    for (int o = LR; o < 64; o <<= 1) {
+      a.x += __shfl_xor(a.x, o, 64);
+      a.y += __shfl_xor(a.y, o, 64);
+      a.z += __shfl_xor(a.z, o, 64);
+      a.w += __shfl_xor(a.w, o, 64);
     }
-    const float f = __builtin_amdgcn_exp2f(m - M);
-    L += f * P.part_ml[row * 2 + 1];
-    a += f * (act ? P.part_acc[row * D + lane] : 0.f);
-  }
-  if (act) {
-    T* o = reinterpret_cast<T*>(P.o) + ((int64_t)t * P.hq + h) * D;
-    Elem<T>::store(o, lane, L > 0.f ? a / L : 0.f);
+    if (sub == 0) {
+      T* o = reinterpret_cast<T*>(P.o) + ((int64_t)(tb + k * stride) * P.hq + h) * D + dim;
+      const float r[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) Elem<T>::store(o, i, L > 0.f ? r[i] / L : 0.f);
+    }
   }
 }
 
 hipError_t launch_attn_combine(int dtype, int head_dim, const AttnCombine& p, hipStream_t s) {
   if (p.n_tokens == 0) return hipSuccess;
-  dim3 grid((p.n_tokens * p.hq + 3) / 4), block(256);
+  const int64_t waves = (int64_t)p.n_tokens * p.hq;
+  const int K = (int)std::min<int64_t>(64, (waves + COMBINE_WAVES - 1) / COMBINE_WAVES);
+  const int stride = (p.n_tokens + K - 1) / K;
+  dim3 grid((unsigned)(((int64_t)stride * p.hq + 3) / 4)), block(256);
   if (dtype == 0) {
-    if (head_dim == 32) hipLaunchKernelGGL((attn_combine_kernel<float, 32>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((attn_combine_kernel<float, 64>), grid, block, 0, s, p);
+    if (head_dim == 32) hipLaunchKernelGGL((attn_combine_kernel<float, 32>), grid, block, 0, s, p, stride, K);
+    else hipLaunchKernelGGL((attn_combine_kernel<float, 64>), grid, block, 0, s, p, stride, K);
   } else {
-    if (head_dim == 32) hipLaunchKernelGGL((attn_combine_kernel<bf16, 32>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((attn_combine_kernel<bf16, 64>), grid, block, 0, s, p);
+    if (head_dim == 32) hipLaunchKernelGGL((attn_combine_kernel<bf16, 32>), grid, block, 0, s, p, stride, K);
+    else hipLaunchKernelGGL((attn_combine_kernel<bf16, 64>), grid, block, 0, s, p, stride, K);
   }
   return hipGetLastError();
 }

@@ -212,3 +212,40 @@ def test_prefill_score_range(hq, hkv, window, scale):
         ref = O.attention(s, seq, pos, q.double().numpy(), k.float().numpy(), wl.v_pool.float().numpy(), wl.page_table,
                           None if sinks is None else sinks.numpy())
         PT.check("o", o.float().cpu().double().numpy().reshape(ref.shape), ref, "bf16")
+
+
+@pytest.mark.parametrize("case", ["many_seqs", "many_tokens", "one_long", "wave_edges"])
+def test_plan_and_combine_edges(case):
+    """Sizes at which the plan and the merge of splits change form: more
+    sequences than are searched in LDS (2048), more tokens than one per thread
+    (4096) and than one token per wavefront of the merge (65536 / 16 heads), one
+    token with more splits than a wavefront has lanes, and split counts around a
+    wavefront's rows per load. Chunks of 1-3 tokens stay on the split path."""
+    s = replace(W.GPT_OSS_20B, hidden=256, n_q_heads=16, n_kv_heads=2, window=0)
+    rng = np.random.default_rng(11)
+    if case == "many_seqs":
+        lens, q = rng.integers(0, 40, 2100), rng.integers(1, 3, 2100)
+    elif case == "many_tokens":
+        lens, q = rng.integers(0, 60, 1500), rng.integers(2, 5, 1500)
+    elif case == "one_long":
+        lens, q = np.array([9001]), np.array([1])
+    else:
+        lens, q = np.array([15, 16, 63, 64, 500, 1023, 1024, 2100, 0]), np.array([1, 1, 2, 1, 3, 1, 1, 1, 1])
+    wl = W.custom(s, [int(x) for x in lens], [int(x) for x in q], 1191, weights=False)
+    T = wl.n_tokens
+    if case == "many_tokens":
+        assert T > 4096 and T * s.n_q_heads > 65536
+    qv = torch.from_numpy(rng.standard_normal((T, s.n_q_heads, 64)).astype(np.float32)).to(torch.bfloat16)
+    sinks = torch.linspace(-2, 2, s.n_q_heads)
+    o = torch.empty((T, s.n_q_heads * 64), dtype=torch.bfloat16, device="cuda")
+    ws = mcpu.workspace(mcpu.paged_attention_workspace_size(s, wl.batch, T))
+    mcpu.paged_attention(s, sinks.cuda(), mcpu.KVPool(s, wl.k_pool.cuda(), wl.v_pool.cuda()),
+                         torch.from_numpy(wl.page_table).cuda(), torch.from_numpy(wl.seq_lens).cuda(),
+                         torch.from_numpy(wl.cu_q).cuda(), wl.seq_lens, wl.cu_q, qv.cuda(), o, ws)
+    torch.cuda.synchronize()
+    assert mcpu.mcpu_check_device_errors(ws) == 0
+    seq = np.repeat(np.arange(wl.batch), wl.q_lens)
+    pos = np.concatenate([np.arange(l, l + n) for l, n in zip(wl.seq_lens, wl.q_lens)])
+    ref = O.attention(s, seq, pos, qv.double().numpy(), wl.k_pool.float().numpy(), wl.v_pool.float().numpy(),
+                      wl.page_table, sinks.numpy())
+    PT.check("o", o.float().cpu().double().numpy().reshape(ref.shape), ref, "bf16")
