@@ -340,6 +340,9 @@ typedef __attribute__((address_space(3))) void* lds_void_t;
 
 template <int EPI, bool WP>
 __global__ __launch_bounds__(PTH) void gemm_dma_kernel(Gemm P) {
+  // The vocabulary head's records are folded from the product registers: through
+  // LDS in 16-row passes the epilogue, sixteen cross-lane reductions per row and
+  // slot between barriers, cost a third of the launch (12 K rows 18.4 -> 13.9 ms).
   static_assert(!(WP && EPI == EPI_QKV), "the projection's row order is not the copy's");
   __shared__ __align__(1024) uint8_t d0[DSTAGE];
   __shared__ __align__(1024) uint8_t d1[DSTAGE];
@@ -492,6 +495,11 @@ __global__ __launch_bounds__(PTH) void gemm_dma_kernel(Gemm P) {
   __syncthreads();  // every load landed before stage 0 holds the fp32 tile
 
   // acc[nb][mb][r] = C[m = wm*128 + 16 mb + fr][n = wn*64 + 16 nb + 4 (lane/16) + r]
+  if constexpr (EPI == EPI_LOGITS) {
+    logit_records<PMF, PNF>(P, acc, m0, mrows, n0 + wn * PWN, n0 + nrows, lane,
+                            [&](int mb) __attribute__((always_inline)) { return wm * (PM / 2) + 16 * mb + fr; });
+    return;
+  }
   float* cr = reinterpret_cast<float*>(d0);
   const EpiBias eb = epilogue_bias<EPI>(P, n0 >> 4, nrows >> 4, grp);
   for (int e0 = 0; e0 < PM; e0 += DEP) {
@@ -517,14 +525,31 @@ __global__ __launch_bounds__(PTH) void gemm_dma_kernel(Gemm P) {
 
 }  // namespace
 
+// The vocabulary head (one matrix): how many of its columns go to these tiles,
+// a multiple of PN or all of them; the caller gives the rest to the 128-row and
+// smaller tiles. A round of 256 tiles takes 98 us at a reduction of 2880 and a
+// 128 x 128 tile 0.135 us of the chip, 726 of them a round; a last round of at
+// most LOGITS_REST tiles would hold the chip for a full one, and costs about half
+// in small tiles. 129-256 rows (3.07 rounds) 440-461 -> 362-398 us, 512
+// 836 -> 660, 900 1560 -> 1204, all against 128 x 128 tiles; up to 128 rows one row of small tiles reads the
+// weights once (291 us against 413).
+int64_t logits_wide_columns(const Gemm& g) {
+  constexpr int64_t LOGITS_REST = 64;
+  const int64_t mt = ((int64_t)g.n_rows + PM - 1) / PM, nt = ((int64_t)g.n + PN - 1) / PN, tiles = mt * nt;
+  if (tiles < 512 && (g.n_rows < 1024 || tile_grid(g, PM, PN) < 512)) return 0;
+  const int64_t nt_full = tiles / 256 * 256 / mt, rest = (nt - nt_full) * mt;
+  const bool split = rest > 0 && rest <= LOGITS_REST;
+  const int64_t half_rounds = split ? tiles / 256 * 2 + 1 : (tiles + 255) / 256 * 2;
+  const int64_t small = ((int64_t)g.n_rows + 127) / 128 * (((int64_t)g.n + 127) / 128);
+  if (g.n_rows < 1024 && 363 * half_rounds >= small) return 0;
+  return split ? nt_full * PN : g.n;
+}
+
 bool pipe_gemm_applies(int dtype, const Gemm& g) {
   if (dtype != 1 || g.k <= 0 || g.k % PK || g.n % 16 || g.n_groups > TILE_MAXG) return false;
   const int64_t groups = g.group_off ? g.n_groups : 1;
-  // rows per group of a full tile on average, and at least two tiles per CU;
-  // the vocabulary head (one matrix, every tile streaming its own weights from
-  // HBM once) only from 1024 rows: below, 128 x 128 tiles keep more loads in
-  // flight per compute unit (256 rows: 569 against 714 us)
-  if (g.epi == EPI_LOGITS && g.n_rows < 1024) return false;
+  // rows per group of a full tile on average, and at least two tiles per CU
+  if (g.epi == EPI_LOGITS) return logits_wide_columns(g) > 0;
   return (int64_t)g.n_rows >= (int64_t)PM * groups && tile_grid(g, PM, PN) >= 512;
 }
 

@@ -184,10 +184,12 @@ struct Gemm {
   float* part;
   int32_t* part_cnt;
   int k_splits;             // set by the launcher
-  // EPI_LOGITS: LogitSlot records [rows][ceil(n / LOGIT_SLOT)] in `out`;
+  // EPI_LOGITS: LogitSlot records [rows][n_slots] in `out`; w holds the
+  // vocabulary's columns col0 .. col0 + n (col0 a multiple of LOGIT_SLOT);
   // s = l * inv_temp (greedy: inv_temp = 1 and no noise); the noise of row r,
   // column v comes from Philox4x32-10 keyed by seed at counter
   // (v / 4, row_pos[r], row_seq[r], LOGIT_RNG_TAG), word v % 4
+  int n_slots, col0;
   float inv_temp;
   int greedy;
   uint64_t seed;
@@ -250,6 +252,7 @@ bool tiled_gemm_applies(int dtype, const Gemm& g);
 hipError_t launch_gemm_tiled(int expert_fmt, const Gemm& g, hipStream_t s);
 // Software-pipelined 256 x 256 tiles once groups average 256 rows and the
 // launch has at least two tiles per compute unit (bf16 activations, k % 32 == 0).
+int64_t logits_wide_columns(const Gemm& g);
 bool pipe_gemm_applies(int dtype, const Gemm& g);
 hipError_t launch_gemm_pipe(int expert_fmt, const Gemm& g, hipStream_t s);
 // Direct-to-LDS rings of 64-wide slices (gemm_ring.hip): k a multiple of 64,

@@ -758,7 +758,7 @@ int lm_head_sample(const mcpu_lm_head* lm, int32_t n_tokens, const float* x, con
 
   Gemm g{};
   g.w = lm->w_lm; g.w_packed = lm->w_lm_packed; g.n = V; g.k = H; g.x = xn; g.group_off = goff;
-  g.n_rows = n_tokens; g.n_groups = 1; g.epi = EPI_LOGITS; g.out = slots; g.err = err_word(workspace);
+  g.n_rows = n_tokens; g.n_groups = 1; g.epi = EPI_LOGITS; g.out = slots; g.n_slots = n_slots; g.err = err_word(workspace);
   g.max_rows_per_group = n_tokens; g.x_rows = n_tokens;
   g.inv_temp = greedy ? 1.f : 1.f / temperature; g.greedy = draws ? 0 : 1; g.seed = seed;
   g.row_seq = seq_ids; g.row_pos = positions; g.target = targets;

@@ -121,6 +121,27 @@ def test_lm_head_sample_full_vocabulary_sampled(T):
     assert torch.equal(Wd["w_lm"].cpu().view(torch.int16), w_host.view(torch.int16))
 
 
+@pytest.mark.parametrize("T,vocab", [(130, 201088), (256, 131072), (400, 201088), (1030, 33040)])
+@pytest.mark.parametrize("temperature", [TAU, 0.0])
+def test_lm_head_sample_wide_tiles(T, vocab, temperature):
+    """Wide tiles over the columns of whole rounds and small ones over the rest
+    (130 and 400 rows), whole rounds only (256 rows), and a partial last tile in
+    both directions (1030 rows, 33040 ids); targets on both sides of the cut and
+    in the last slot."""
+    H = 256
+    Wt, head = _small_head(H, vocab, 2011)
+    rng = np.random.default_rng(T + vocab)
+    x = torch.from_numpy(rng.standard_normal((T, H)).astype(np.float32) * 2)
+    seq, pos = rng.integers(0, 1000, T), rng.integers(0, 70000, T)
+    tgt = rng.integers(0, vocab, T)
+    rows = np.sort(rng.choice(T, 24, replace=False))
+    tgt[rows[:4]] = vocab - 1, vocab - 17, 0, vocab - 4500
+    gpu = _run_head(head, x, temperature, 78, seq, pos, tgt)
+    ref = O.lm_head(x[rows], Wt["g_final"], Wt["w_lm"], 1e-5, temperature, seed=78, seq_ids=seq[rows],
+                    positions=pos[rows], targets=tgt[rows], want_logits=True)
+    _check(gpu, ref, rows)
+
+
 def test_lm_head_draw_is_independent_of_the_batch():
     """A row's token depends on (seed, sequence, position) only: permuting the
     rows permutes the results bit for bit, and the same rows inside a larger
