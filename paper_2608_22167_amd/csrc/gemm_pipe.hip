@@ -25,7 +25,8 @@
 // write (rows r and r + 2) covers all eight 16-byte bank groups of a 128-byte
 // bank row; with rows 80 or 144 B apart both take twice the LDS cycles.
 //
-// MXFP4 weights are decoded while they are staged (the packed e2m1 -> bf16
+// MXFP4 weights (those that the ring kernel, gemm_ring.hip, does not take) are
+// decoded while they are staged (the packed e2m1 -> bf16
 // conversion with the block scale; exact). The finished fp32 tile goes through
 // LDS to the fused epilogue, 32 rows at a time.
 #include <type_traits>

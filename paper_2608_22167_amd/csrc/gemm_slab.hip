@@ -1,6 +1,7 @@
 // Weight-streaming slabs for grouped GEMMs with up to about a hundred token
 // rows per weight matrix (gfx950, bf16 activations, bf16 or MXFP4 weights):
-// the expert projections of decode batches of up to a few thousand tokens.
+// the bf16 expert projections of decode batches, and MXFP4 ones of fewer than 8
+// rows in all or that the ring kernel (gemm_ring.hip) does not take.
 //
 // There each weight byte meets only a few dozen token rows, so the bound is
 // HBM, and the kernel's job is to keep enough weight bytes in flight. A

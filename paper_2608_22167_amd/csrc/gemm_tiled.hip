@@ -10,7 +10,8 @@
 // and each wavefront multiplies a (BM/2) x (BN/2) quadrant out of LDS with the
 // 16x16x32 bf16 matrix-core product while the next R slices are in flight
 // in a ring of R register sets (deep rings for weight-streaming shapes, whose
-// time goes into HBM latency). MXFP4 weights are decoded once, while they are staged, with the
+// time goes into HBM latency). MXFP4 weights (those that
+// the ring kernel, gemm_ring.hip, does not take) are decoded once, while they are staged, with the
 // packed e2m1 -> bf16 conversion that applies the block scale (exact: every
 // product of an e2m1 value and a scale in [2^-125, 2^125] is a normal
 // bfloat16).

@@ -262,7 +262,7 @@ hipError_t launch_gemm_ring(int expert_fmt, const Gemm& g, hipStream_t s);
 // Weight slabs (gemm_slab.hip): grouped GEMMs with bf16 activations whose
 // groups are too short for tiles (bf16 weights, under TILED_MIN_ROWS rows per
 // group) or whose MXFP4 weights dominate the traffic (up to SLAB_MAX_ROWS_FP4
-// rows per group on average); k a multiple of 64.
+// rows per group on average, where ring_gemm_applies does not hold); k a multiple of 64.
 constexpr int SLAB_MAX_ROWS_FP4 = 96;
 bool slab_gemm_applies(int dtype, int expert_fmt, const Gemm& g);
 // One bf16 matrix against at most SPLIT_MAX_ROWS token rows: the slabs also
