@@ -142,6 +142,28 @@ def test_lm_head_sample_wide_tiles(T, vocab, temperature):
     _check(gpu, ref, rows)
 
 
+@pytest.mark.parametrize("T,vocab,cut", [(256, 147232, 131072), (512, 73536, 65536), (1000, 36768, 32768),
+                                         (4096, 33728, 32768), (200, 32160, 0)])
+@pytest.mark.parametrize("temperature", [TAU, 0.0])
+def test_lm_head_sample_columns_of_160(T, vocab, cut, temperature):
+    """Columns (all of them, or those from `cut` on that whole rounds of wide
+    tiles leave over) that are a multiple of 160 and not of 128 and make enough
+    tiles for the 64-row ones: every 64-column record is written once. Targets
+    in columns 128-223 of runs of 320 columns."""
+    H = 256
+    Wt, head = _small_head(H, vocab, 2021)
+    rng = np.random.default_rng(T + vocab)
+    x = torch.from_numpy(rng.standard_normal((T, H)).astype(np.float32) * 2)
+    seq, pos = rng.integers(0, 1000, T), rng.integers(0, 70000, T)
+    assert (vocab - cut) % 160 == 0 and (vocab - cut) % 128
+    tgt = cut + 320 * rng.integers(0, (vocab - cut) // 320, T) + rng.integers(128, 224, T)
+    rows = np.sort(rng.choice(T, 24, replace=False))
+    gpu = _run_head(head, x, temperature, 79, seq, pos, tgt)
+    ref = O.lm_head(x[rows], Wt["g_final"], Wt["w_lm"], 1e-5, temperature, seed=79, seq_ids=seq[rows],
+                    positions=pos[rows], targets=tgt[rows], want_logits=True)
+    _check(gpu, ref, rows)
+
+
 def test_lm_head_draw_is_independent_of_the_batch():
     """A row's token depends on (seed, sequence, position) only: permuting the
     rows permutes the results bit for bit, and the same rows inside a larger
