@@ -936,9 +936,12 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefill P) {
 // that the lanes of a half tile read all banks.
 //
 // The maximum of a column is raised only when a lane's share of a step's
-// weights would pass 2^40 (WEIGHT_LIMIT): below that, sums and accumulators stay far inside fp32
-// and a bf16 weight's relative error does not depend on its exponent, so the
-// rescale of the accumulators is rare instead of per step.
+// weights would pass 2^8 (WEIGHT_LIMIT, the bound of a single weight in the
+// kernel above): the accumulators keep fp32's headroom for values up to 2^108
+// and more, and the largest weights are near one, where they are 1 exactly
+// whenever the maximum was just raised. A limit of 2^40 was no faster, lost
+// values beyond 2^75 to infinity and doubled the squared error of columns whose
+// first visible keys score low.
 //
 // Bound: the vector pipe, about 126 instructions per wavefront and step (the 64
 // x 32 exponentials cost two slots each). Measured against the 16 x 16 tiles,
@@ -1039,7 +1042,7 @@ __global__ __launch_bounds__(256) void attn_prefill_wide_kernel(AttnPrefill P) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t)(stg + wave * PB + 1024 * u), 16, vo[u], 0, 0, 0);
   };
 
-  constexpr float WEIGHT_LIMIT = 0x1p40f;  // of a lane's 16 weights in a step
+  constexpr float WEIGHT_LIMIT = 0x1p8f;  // of a lane's 16 weights in a step
   float m_run[2], m_sub[2], limit[2], l[2];  // limit: -inf until a key is visible
   f32x16 acc[2][2];  // [dim tile][column tile]
 #pragma unroll

@@ -214,6 +214,37 @@ def test_prefill_score_range(hq, hkv, window, scale):
         PT.check("o", o.float().cpu().double().numpy().reshape(ref.shape), ref, "bf16")
 
 
+@pytest.mark.parametrize("window", [0, 128])
+def test_prefill_large_values(window):
+    """Values of 2^108 behind scores that climb by about four powers of two per
+    page: weights stay within 2^8 of the running maximum, so the accumulators
+    stay below 2^8 x 2^111 x a few keys, in range of fp32 (weights let run to
+    2^20 would leave it)."""
+    s = replace(W.GPT_OSS_20B, hidden=256, n_q_heads=16, n_kv_heads=2, window=window)
+    wl = W.custom(s, [0, 100, 300], [17, 40, 70], 1192, weights=False)
+    rng = np.random.default_rng(8)
+    T = wl.n_tokens
+    d = torch.from_numpy(rng.choice([-1.0, 1.0], 64).astype(np.float32))
+    q = (torch.from_numpy(rng.standard_normal((T, 16, 64)).astype(np.float32)) * 0.1 + d).to(torch.bfloat16)
+    k = wl.k_pool.float() * 0.1
+    for b in range(wl.batch):
+        for lp, page in enumerate(wl.page_table[b]):
+            if page >= 0:
+                k[page] += 0.375 * lp * d.view(8, 1, 8).expand(8, 16, 8).reshape(1, 16, 64)
+    k, v = k.to(torch.bfloat16), (wl.v_pool.float() * 2.0 ** 108).to(torch.bfloat16)
+    o = torch.empty((T, 16 * 64), dtype=torch.bfloat16, device="cuda")
+    ws = mcpu.workspace(mcpu.paged_attention_workspace_size(s, wl.batch, T))
+    mcpu.paged_attention(s, None, mcpu.KVPool(s, k.cuda(), v.cuda()),
+                         torch.from_numpy(wl.page_table).cuda(), torch.from_numpy(wl.seq_lens).cuda(),
+                         torch.from_numpy(wl.cu_q).cuda(), wl.seq_lens, wl.cu_q, q.cuda(), o, ws)
+    torch.cuda.synchronize()
+    assert mcpu.mcpu_check_device_errors(ws) == 0
+    seq = np.repeat(np.arange(wl.batch), wl.q_lens)
+    pos = np.concatenate([np.arange(l, l + n) for l, n in zip(wl.seq_lens, wl.q_lens)])
+    ref = O.attention(s, seq, pos, q.double().numpy(), k.float().numpy(), wl.v_pool.float().numpy(), wl.page_table, None)
+    PT.check("o", (o.double().cpu() * 2.0 ** -108).numpy().reshape(ref.shape), ref, "bf16")
+
+
 @pytest.mark.parametrize("case", ["many_seqs", "many_tokens", "one_long", "wave_edges"])
 def test_plan_and_combine_edges(case):
     """Sizes at which the plan and the merge of splits change form: more
