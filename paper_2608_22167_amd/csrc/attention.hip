@@ -1183,9 +1183,15 @@ __global__ __launch_bounds__(256) void attn_prefill_wide_kernel(AttnPrefill P) {
   if (n_steps > 0) {
     auto publish = [&]() __attribute__((always_inline)) {
       constexpr int N = 2 * (PRS - 3);
+      // the barrier hands the stages over: this wavefront's reads of the step's
+      // stage have returned (lgkmcnt), its loads of step s + 2 have landed, and
+      // the empty asm keeps LDS accesses on their side of it (to the compiler
+      // the barrier itself touches no memory)
       __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_waitcnt(N | (7 << 4) | (15 << 8));  // vmcnt(N) expcnt(7) lgkmcnt(15)
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(N | (7 << 4));  // vmcnt(N) expcnt(7) lgkmcnt(0)
       __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
     };
 #pragma unroll
