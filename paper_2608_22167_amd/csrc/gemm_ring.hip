@@ -140,6 +140,7 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
   constexpr int UN = CS * SPU;                              // slices per unrolled round
   constexpr int GM = BM == 64 ? 8 : BM == 128 ? 4 : 2;  // m-tiles per band
   __shared__ __align__(1024) uint8_t lds[SOFF + SCL];
+  __shared__ int rejected;  // MXFP4: the last item with a rejected scale
   uint8_t* scl = lds + SOFF;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int nk = P.k / RK, kb = P.k / 32, nkp = (nk + UN - 1) / UN * UN;
@@ -341,9 +342,11 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
     u32x2 w[NT];
     float s[NT];
   };
-  // Scales outside [2, 252] raise the error bit and are replaced by 2 (2^-125:
-  // the block contributes nothing), once per item and outside the reduction.
-  auto check_scales = [&](const Item& t) __attribute__((always_inline)) {
+  // Scales outside [2, 252] raise the error bit, once per item and outside the
+  // reduction; the block contributes zero: its scale is staged as 0 and the
+  // item's reduction takes the form that clears such blocks' codes (its own
+  // form, so that the others carry no mask).
+  auto check_scales = [&](const Item& t, int item) __attribute__((always_inline)) {
     if constexpr (WF == 1) {
       const int pieces = min(BN, P.n - t.n0) * kb / 16;  // whole: n is a multiple of 16, k of 64
       for (int p = tid; p < pieces; p += NW * 64) {
@@ -361,11 +364,12 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
 #pragma unroll
             for (int b = 0; b < 32; b += 8)
               if (((w[j] >> b) & 255u) - 2u > 250u) {
-                w[j] = (w[j] & ~(255u << b)) | (2u << b);
+                w[j] &= ~(255u << b);
                 any = true;
               }
           if (any) {
             *reinterpret_cast<u32x4*>(scl + 16 * p) = w;
+            rejected = item;
             set_error(P.err, 16);
           }
         }
@@ -387,18 +391,21 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
   // rows), nkp slots. While slice i is multiplied, the head of slice i + 1 (its
   // first weight fragments or codes and two token fragments) is read into the
   // other of two register sets.
-  auto reduce = [&](auto MV_) __attribute__((always_inline)) {
+  auto reduce = [&](auto MV_, auto CLEAR_) __attribute__((always_inline)) {
     constexpr int MV = decltype(MV_)::value, U = 2 * MV;  // U steps of NT products per slice
+    constexpr bool CLEAR = decltype(CLEAR_)::value;       // MXFP4: clear the codes of rejected blocks
+    auto codes = [&](Codes& k, int nb, const uint8_t* at, uint32_t scale) __attribute__((always_inline)) {
+      k.w[nb] = lds8(at);
+      if constexpr (CLEAR) k.w[nb] &= scale ? ~0u : 0u;
+      k.s[nb] = __uint_as_float((CLEAR && !scale ? 127u : scale) << 23);
+    };
     u32x4 bh[2][2], ah[2][NT];
     Codes kc[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) bh[0][u] = xread(0, u / MV, u % MV);
     if constexpr (WF == 1) {
 #pragma unroll
-      for (int nb = 0; nb < NT; ++nb) {
-        kc[0].w[nb] = lds8(lds + wo[nb]);
-        kc[0].s[nb] = __uint_as_float((uint32_t)scl[so[nb]] << 23);
-      }
+      for (int nb = 0; nb < NT; ++nb) codes(kc[0], nb, lds + wo[nb], scl[so[nb]]);
     } else {
 #pragma unroll
       for (int nb = 0; nb < NT; ++nb) ah[0][nb] = wread(0, 0, nb);
@@ -423,10 +430,8 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
               if (c == 0) a1[nb] = wread(WC, 1, nb);
               else ah[H ^ 1][nb] = wread(WN_, 0, nb);
             } else {
-              if (c == 0) {
-                kc[H ^ 1].w[nb] = lds8(lds + (wo[nb] ^ (32u * (H ^ 1))) + WN_ * WB);  // the slice's half of the rows
-                kc[H ^ 1].s[nb] = __uint_as_float((uint32_t)scl[so[nb] + sn] << 23);
-              }
+              if (c == 0)  // the slice's half of the rows
+                codes(kc[H ^ 1], nb, lds + (wo[nb] ^ (32u * (H ^ 1))) + WN_ * WB, scl[so[nb] + sn]);
             }
           }
         if (s == 0) {
@@ -476,9 +481,13 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
   };
 
   Item cur = item_of(idx);
+  if constexpr (WF == 1) {
+    if (tid == 0) rejected = -1;
+    __builtin_amdgcn_s_waitcnt((15) | (7 << 4) | (3 << 14));  // lgkmcnt(0)
+  }
   while (true) {
     meet();  // the item's first slices and its scales have landed
-    check_scales(cur);
+    check_scales(cur, idx);
     meet();
     if constexpr (WF == 1) {
 #pragma unroll
@@ -493,15 +502,20 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
     // wavefront meets the same barriers
     const int m0 = cur.m0, mrows = cur.mrows, n0 = cur.n0;
     const int mv = uniform((mrows + 16 * WM - 1) / (16 * WM));
-    if constexpr (MT == 4) {
-      if (mv == 1) reduce(std::integral_constant<int, 1>{});
-      else if (mv == 2) reduce(std::integral_constant<int, 2>{});
-      else if (mv == 3) reduce(std::integral_constant<int, 3>{});
-      else reduce(std::integral_constant<int, 4>{});
+    constexpr std::false_type keep{};
+    bool clear = false;
+    if constexpr (WF == 1) clear = uniform(rejected) == idx;
+    if (WF == 1 && __builtin_expect(clear, 0)) {  // all fragments, also those without rows (their sums are dropped)
+      if constexpr (WF == 1) reduce(std::integral_constant<int, MT>{}, std::true_type{});
+    } else if constexpr (MT == 4) {
+      if (mv == 1) reduce(std::integral_constant<int, 1>{}, keep);
+      else if (mv == 2) reduce(std::integral_constant<int, 2>{}, keep);
+      else if (mv == 3) reduce(std::integral_constant<int, 3>{}, keep);
+      else reduce(std::integral_constant<int, 4>{}, keep);
     } else {
       static_assert(MT == 2, "two or four token fragments per wavefront");
-      if (mv == 1) reduce(std::integral_constant<int, 1>{});
-      else reduce(std::integral_constant<int, 2>{});
+      if (mv == 1) reduce(std::integral_constant<int, 1>{}, keep);
+      else reduce(std::integral_constant<int, 2>{}, keep);
     }
 
     // ---- epilogue, straight from the accumulators -----------------------------

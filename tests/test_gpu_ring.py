@@ -72,8 +72,42 @@ def test_mxfp4_rejected_scales_contribute_nothing(T):
     _, want, err0 = _forced_moe(s, zero, force, 12)
     _, got, err = _forced_moe(s, bad, force, 12)
     assert err0 == 0 and err & mcpu.DEVERR_MXFP4
-    # a rejected block weighs 6 x 2^-125 at most: far below one ulp of any sum here
-    np.testing.assert_allclose(got, want, rtol=0, atol=1e-30)
+    np.testing.assert_array_equal(got, want)
+
+
+@pytest.mark.parametrize("T", [40, 400, 2400])  # 10, 100 and 600 rows per expert
+@pytest.mark.parametrize("key", ["w_gu", "w_d"])
+def test_mxfp4_rejected_blocks_are_exactly_zero(key, T):
+    """One matrix holds codes 6 in blocks of rejected scales and zeros elsewhere,
+    so the experts add exactly nothing. Gate/up: a remainder of 2^-125 would
+    come back through down weights of 6 x 2^125. Down: the rows are zero and the
+    activations 56 (gate and up biases of 7), so a remainder is the output."""
+    s = _shape(576, 576)
+    wl = W.custom(s, [4], [1], 2112)
+    rng = np.random.default_rng(6)
+    w = {k: v.clone() for k, v in wl.weights.items()}
+    for b in ("b_gu", "b_d"):
+        w[b].zero_()
+    w["w_d_codes"].fill_(0x77)
+    w["w_d_scales"].fill_(252)
+    sc, codes = w[key + "_scales"], w[key + "_codes"]
+    sc.fill_(120)
+    codes.zero_()
+    bad = rng.random(tuple(sc.shape)) < 0.05
+    bad[:, 0, 0] = bad[:, -1, -1] = True
+    sc[torch.from_numpy(bad)] = torch.from_numpy(rng.choice([0, 1, 253, 254, 255], bad.sum()).astype(np.uint8))
+    codes[torch.from_numpy(np.repeat(bad, 16, axis=2))] = 0x77
+    h = W.synth_normal(14, 5, (T, s.hidden))
+    if key == "w_d":
+        w["b_gu"].fill_(7.0)
+        h.zero_()
+    out = torch.full((T, s.hidden), 7.0, device="cuda")
+    ws = mcpu.workspace(mcpu.moe_forward_workspace_size(s, T))
+    mcpu.moe_forward(s, mcpu.DeviceWeights(s, w), h.cuda(), out, None, None,
+                     torch.from_numpy(rng.integers(0, 8, size=(T, 2)).astype(np.int32)).cuda(), ws)
+    torch.cuda.synchronize()
+    assert mcpu.mcpu_check_device_errors(ws) & mcpu.DEVERR_MXFP4
+    assert torch.equal(out.cpu(), h)
 
 
 @pytest.mark.parametrize("pack", [False, True])
