@@ -1263,18 +1263,22 @@ static hipError_t prefill_impl(int group, const AttnPrefill& p, hipStream_t s) {
   dim3 grid((unsigned)(p.n_blocks * p.hkv)), block(256);
   // bf16 with head dim 64 takes the wide products (figures at the kernel);
   // float has no such tile, and only the smallest configuration has head dim 32.
+  // Its pages go to LDS by 16-byte direct loads, which are used on 16-byte
+  // aligned pools only.
   if constexpr (sizeof(T) == 2 && D == 64) {
-    switch (group) {
-      case 4: hipLaunchKernelGGL(attn_prefill_wide_kernel<4>, grid, block, 0, s, p); break;
-      case 8: hipLaunchKernelGGL(attn_prefill_wide_kernel<8>, grid, block, 0, s, p); break;
-      default: return hipErrorInvalidValue;
+    if ((uintptr_t)p.k_pool % 16 == 0 && (uintptr_t)p.v_pool % 16 == 0) {
+      switch (group) {
+        case 4: hipLaunchKernelGGL(attn_prefill_wide_kernel<4>, grid, block, 0, s, p); break;
+        case 8: hipLaunchKernelGGL(attn_prefill_wide_kernel<8>, grid, block, 0, s, p); break;
+        default: return hipErrorInvalidValue;
+      }
+      return hipGetLastError();
     }
-  } else {
-    switch (group) {
-      case 4: hipLaunchKernelGGL((attn_prefill_kernel<T, D, 4>), grid, block, 0, s, p); break;
-      case 8: hipLaunchKernelGGL((attn_prefill_kernel<T, D, 8>), grid, block, 0, s, p); break;
-      default: return hipErrorInvalidValue;
-    }
+  }
+  switch (group) {
+    case 4: hipLaunchKernelGGL((attn_prefill_kernel<T, D, 4>), grid, block, 0, s, p); break;
+    case 8: hipLaunchKernelGGL((attn_prefill_kernel<T, D, 8>), grid, block, 0, s, p); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }

@@ -560,12 +560,13 @@ hipError_t launch_gemm_pipe(int expert_fmt, const Gemm& g, hipStream_t s) {
   if (expert_fmt != 0 && !g.w_scales) return hipErrorInvalidValue;
   dim3 gd((unsigned)grid), bd(PTH);
   // direct loads address rows with 32-bit offsets: from the tile's first row,
-  // or from x itself when rows are gathered, and within one group's weights
+  // or from x itself when rows are gathered, and within one group's weights,
+  // and are used on 16-byte aligned matrices only
   const int64_t xr = g.row_src ? (g.x_rows > 0 ? g.x_rows : g.n_rows) : PM;
-  const bool dma = xr * g.k * 2 < (1LL << 31) && (int64_t)g.n * g.k * 2 < (1LL << 31);
+  const bool dma = xr * g.k * 2 < (1LL << 31) && (int64_t)g.n * g.k * 2 < (1LL << 31) && (uintptr_t)g.w % 16 == 0;
   // the streaming-order weight copy, when given, for every epilogue but the
   // projection's (whose row order is its own)
-  const bool wp = g.w_packed && g.k % PK == 0 && (int64_t)(g.n / 16) * ((g.k + 127) / 128) * 4096 < (1LL << 31);
+  const bool wp = g.w_packed && (uintptr_t)g.w_packed % 16 == 0 && g.k % PK == 0 && (int64_t)(g.n / 16) * ((g.k + 127) / 128) * 4096 < (1LL << 31);
 #define PIPE_LAUNCH(E)                                                                          \
   do {                                                                                          \
     if (expert_fmt != 0) hipLaunchKernelGGL((gemm_pipe_kernel<E, 1>), gd, bd, 0, s, g);        \

@@ -634,6 +634,9 @@ bool ring_gemm_applies(int dtype, int expert_fmt, const Gemm& g) {
     return g.n_rows >= 8 && g.k <= 32 * RING_MAX_KB && g.w_scales && (uintptr_t)g.w_scales % 16 == 0 &&
            (uintptr_t)g.w % 16 == 0 && (g.epi == EPI_SWIGLU || g.epi == EPI_BIAS);
   if (g.w_packed && (int64_t)(g.n / 16) * ((g.k + 127) / 128) * 4096 >= (1LL << 31)) return false;
+  // 16-byte direct loads to LDS are used on 16-byte aligned matrices only (token
+  // rows come from the workspace); others keep the kernels that load to registers
+  if ((uintptr_t)g.w % 16 || (uintptr_t)g.w_packed % 16) return false;
   if (g.epi == EPI_QKV && (g.n % 64 || (g.head_dim != 32 && g.head_dim != 64))) return false;
   if (pipe_gemm_applies(dtype, g)) return false;
   const int64_t groups = g.group_off ? g.n_groups : 1, tiles = ((int64_t)g.n_rows + 127) / 128 * ((g.n + 127) / 128);

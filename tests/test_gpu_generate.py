@@ -164,6 +164,25 @@ def test_lm_head_sample_columns_of_160(T, vocab, cut, temperature):
     _check(gpu, ref, rows)
 
 
+def test_lm_head_sample_off_16_byte_boundary():
+    """Vocabulary rows that start 8 bytes past a 16-byte boundary, which direct
+    loads to LDS are not used on, at a size of the wide tiles."""
+    H, vocab, T = 256, 131072, 256
+    Wt = W.lm_weights_host(2011, H, vocab, embed=False)
+    buf = torch.empty(vocab * H + 4, dtype=torch.bfloat16, device="cuda")
+    buf[4:].copy_(Wt["w_lm"].view(-1))
+    head = mcpu.DeviceLmHead(Wt["g_final"], buf[4:].view(vocab, H), pack=False)
+    assert head.struct.w_lm % 16 == 8
+    rng = np.random.default_rng(6)
+    x = torch.from_numpy(rng.standard_normal((T, H)).astype(np.float32) * 2)
+    seq, pos, tgt = rng.integers(0, 1000, T), rng.integers(0, 70000, T), rng.integers(0, vocab, T)
+    rows = np.sort(rng.choice(T, 24, replace=False))
+    gpu = _run_head(head, x, TAU, 80, seq, pos, tgt)
+    ref = O.lm_head(x[rows], Wt["g_final"], Wt["w_lm"], 1e-5, TAU, seed=80, seq_ids=seq[rows], positions=pos[rows],
+                    targets=tgt[rows], want_logits=True)
+    _check(gpu, ref, rows)
+
+
 def test_lm_head_draw_is_independent_of_the_batch():
     """A row's token depends on (seed, sequence, position) only: permuting the
     rows permutes the results bit for bit, and the same rows inside a larger

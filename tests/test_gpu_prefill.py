@@ -245,6 +245,34 @@ def test_prefill_large_values(window):
     PT.check("o", (o.double().cpu() * 2.0 ** -108).numpy().reshape(ref.shape), ref, "bf16")
 
 
+@pytest.mark.parametrize("hq,hkv", [(16, 2), (8, 2)])
+def test_prefill_pools_off_16_byte_boundaries(hq, hkv):
+    """Pools that start 8 bytes past a 16-byte boundary, which direct loads to
+    LDS are not used on: chunks of one block, past one and behind cached keys."""
+    s = replace(W.GPT_OSS_20B, hidden=256, n_q_heads=hq, n_kv_heads=hkv, window=0)
+    wl = W.custom(s, [0, 13, 500], [17, 70, 40], 1193, weights=False)
+    T = wl.n_tokens
+    q = W.synth_normal(1193, 40, (T, hq, 64), dtype=torch.bfloat16)
+    pools = []
+    for p in (wl.k_pool, wl.v_pool):
+        buf = torch.empty(p.numel() + 4, dtype=p.dtype, device="cuda")
+        buf[4:].copy_(p.view(-1))
+        pools.append(buf[4:].view(p.shape))
+        assert pools[-1].data_ptr() % 16 == 8
+    o = torch.empty((T, hq * 64), dtype=torch.bfloat16, device="cuda")
+    ws = mcpu.workspace(mcpu.paged_attention_workspace_size(s, wl.batch, T))
+    mcpu.paged_attention(s, None, mcpu.KVPool(s, *pools), torch.from_numpy(wl.page_table).cuda(),
+                         torch.from_numpy(wl.seq_lens).cuda(), torch.from_numpy(wl.cu_q).cuda(), wl.seq_lens, wl.cu_q,
+                         q.cuda(), o, ws)
+    torch.cuda.synchronize()
+    assert mcpu.mcpu_check_device_errors(ws) == 0
+    seq = np.repeat(np.arange(wl.batch), wl.q_lens)
+    pos = np.concatenate([np.arange(l, l + n) for l, n in zip(wl.seq_lens, wl.q_lens)])
+    ref = O.attention(s, seq, pos, q.double().numpy(), wl.k_pool.float().numpy(), wl.v_pool.float().numpy(),
+                      wl.page_table, None)
+    PT.check("o", o.float().cpu().double().numpy().reshape(ref.shape), ref, "bf16")
+
+
 @pytest.mark.parametrize("case", ["many_seqs", "many_tokens", "one_long", "wave_edges"])
 def test_plan_and_combine_edges(case):
     """Sizes at which the plan and the merge of splits change form: more

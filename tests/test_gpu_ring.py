@@ -129,6 +129,35 @@ def test_bf16_experts(pack, ffn):
     PT.check("moe out", out.cpu().double().numpy(), O.moe(s, O.Weights(s, wl.weights), h, force_idx=force)["out"], "bf16")
 
 
+def _shifted(t, n=4):
+    """A copy on the GPU that starts n elements (8 bytes in bf16) past a 16-byte boundary."""
+    buf = torch.empty(t.numel() + n, dtype=t.dtype, device="cuda")
+    out = buf[n:].view(t.shape)
+    out.copy_(t)
+    assert out.data_ptr() % 16 and out.is_contiguous()
+    return out
+
+
+@pytest.mark.parametrize("T", [700, 16384])  # about 88 and 2048 rows per expert: ring and 256 x 256 tiles if aligned
+def test_bf16_experts_off_16_byte_boundaries(T):
+    """Matrices that direct loads to LDS are not used on."""
+    s = _shape(576, 576, fmt="dense", top_k=1)
+    wl = W.custom(s, [4], [1], 2122)
+    w = {k: _shifted(v) if k in ("w_gu", "w_d") else v for k, v in wl.weights.items()}
+    dw = mcpu.DeviceWeights(s, w, pack=False)
+    assert dw.struct.w_gu % 16 == 8 and dw.struct.w_d % 16 == 8
+    force = (np.random.default_rng(4).permutation(T) % 8).astype(np.int32)[:, None]
+    h = W.synth_normal(15, 5, (T, s.hidden))
+    out = torch.empty((T, s.hidden), device="cuda")
+    ws = mcpu.workspace(mcpu.moe_forward_workspace_size(s, T))
+    mcpu.moe_forward(s, dw, h.cuda(), out, None, None, torch.from_numpy(force).cuda(), ws)
+    torch.cuda.synchronize()
+    assert mcpu.mcpu_check_device_errors(ws) == 0
+    rows = np.unique(np.concatenate([[0, T - 1], np.random.default_rng(5).choice(T, 90, replace=False)]))
+    ref = O.moe(s, O.Weights(s, wl.weights), h[torch.from_numpy(rows)], force_idx=force[rows])["out"]
+    PT.check("moe out", out.cpu().double().numpy()[rows], ref, "bf16")
+
+
 # 128 x 128 tiles above the dispatch's bound for both projections: 64-wide heads
 # with a ragged last m-tile, and 32-wide ones (two heads a piece, a partial last n-tile)
 @pytest.mark.parametrize("pack", [False, True])
