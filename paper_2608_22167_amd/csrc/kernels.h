@@ -93,6 +93,7 @@ struct AttnCombine {
   const int32_t* split_start;
   const float* sinks;  // [Hq] or nullptr
   int n_tokens, n_splits, hq;
+  int n_dec, max_splits;  // tokens with splits, and the most splits of one (host counts: they choose the form only)
   void* o;             // [T][Hq * D]
 };
 

@@ -126,6 +126,7 @@ int token_pages(int pos, int window) {
 
 struct AttnPlanHost {
   int n_tokens = 0, pps = PPS_MIN, n_splits = 0, max_pos = 0;
+  int n_dec = 0, max_splits = 0;  // tokens on the split path, most splits of one
   int prefill_min_q = 0, prefill_qb = 0, n_blocks = 0;  // chunked-prefill work (0 blocks: none)
 };
 
@@ -172,7 +173,13 @@ int plan_attention(const mcpu_layer_cfg* c, int batch, int max_pages, const int3
   pps = std::min<long long>(pps, PPS_MAX);
   pps = std::max<long long>(pps, (total_pages + SPLIT_EXTRA - 1) / SPLIT_EXTRA);
   long long splits = 0;
-  for (int np : pages) splits += (np + pps - 1) / pps;
+  long long most = 0;
+  for (int np : pages) {
+    splits += (np + pps - 1) / pps;
+    most = std::max(most, (np + pps - 1) / pps);
+  }
+  out->n_dec = (int)pages.size();
+  out->max_splits = (int)most;
   out->n_tokens = T;
   out->pps = (int)pps;
   out->n_splits = (int)splits;
@@ -402,6 +409,7 @@ int run_attention(const mcpu_layer_cfg* c, const float* sinks, mcpu_kv_pool* poo
     AttnCombine cb{};
     cb.part_ml = ab.part_ml; cb.part_acc = ab.part_acc; cb.split_start = ab.split_start; cb.sinks = sinks;
     cb.n_tokens = ph.n_tokens; cb.n_splits = ph.n_splits; cb.hq = c->n_q_heads; cb.o = o;
+    cb.n_dec = ph.n_dec; cb.max_splits = ph.max_splits;
     Timed tm(MCPU_KERNEL_ATTN_COMBINE, st);
     HIP_TRY(launch_attn_combine(c->dtype, c->head_dim, cb, st));
   }

@@ -273,13 +273,14 @@ def test_prefill_pools_off_16_byte_boundaries(hq, hkv):
     PT.check("o", o.float().cpu().double().numpy().reshape(ref.shape), ref, "bf16")
 
 
-@pytest.mark.parametrize("case", ["many_seqs", "many_tokens", "one_long", "wave_edges"])
+@pytest.mark.parametrize("case", ["many_seqs", "many_tokens", "one_long", "wave_edges", "in_order"])
 def test_plan_and_combine_edges(case):
     """Sizes at which the plan and the merge of splits change form: more
     sequences than are searched in LDS (2048), more tokens than one per thread
     (4096) and than one token per wavefront of the merge (65536 / 16 heads), one
-    token with more splits than a wavefront has lanes, and split counts around a
-    wavefront's rows per load. Chunks of 1-3 tokens stay on the split path."""
+    token with more splits than a wavefront has lanes, split counts around a
+    wavefront's rows per load, and one to nine splits among enough tokens to be
+    merged in order. Chunks of 1-3 tokens stay on the split path."""
     s = replace(W.GPT_OSS_20B, hidden=256, n_q_heads=16, n_kv_heads=2, window=0)
     rng = np.random.default_rng(11)
     if case == "many_seqs":
@@ -288,6 +289,8 @@ def test_plan_and_combine_edges(case):
         lens, q = rng.integers(0, 60, 1500), rng.integers(2, 5, 1500)
     elif case == "one_long":
         lens, q = np.array([9001]), np.array([1])
+    elif case == "in_order":
+        lens, q = np.concatenate([rng.integers(0, 40, 500), 255 + 256 * np.arange(9)]), np.ones(509, int)
     else:
         lens, q = np.array([15, 16, 63, 64, 500, 1023, 1024, 2100, 0]), np.array([1, 1, 2, 1, 3, 1, 1, 1, 1])
     wl = W.custom(s, [int(x) for x in lens], [int(x) for x in q], 1191, weights=False)
