@@ -528,12 +528,15 @@ __global__ __launch_bounds__(PTH) void gemm_dma_kernel(Gemm P) {
 
 // The vocabulary head (one matrix): how many of its columns go to these tiles,
 // a multiple of PN or all of them; the caller gives the rest to the 128-row and
-// smaller tiles. A round of 256 tiles takes 98 us at a reduction of 2880 and a
-// 128 x 128 tile 0.135 us of the chip, 726 of them a round; a last round of at
-// most LOGITS_REST tiles would hold the chip for a full one, and costs about half
-// in small tiles. 129-256 rows (3.07 rounds) 440-461 -> 362-398 us, 512
-// 836 -> 660, 900 1560 -> 1204, all against 128 x 128 tiles; up to 128 rows one row of small tiles reads the
-// weights once (291 us against 413).
+// smaller tiles. A round of 256 tiles takes 30 + 0.0229 k us and a 128 x 128 tile
+// 0.0216 + 0.0371 k / 1000 us of the chip (k the reduction; within 6% at k = 256 ..
+// 4096, 257 .. 1023 rows), so short reductions need more rows for the wide tiles. A last
+// round of at most LOGITS_REST tiles would hold the chip for a full one, and costs
+// about half in small tiles. Small -> wide at k = 2880, 201,088 columns: 129-256
+// rows (3.07 rounds) 455-529 -> 361-382 us, 385-512 800 -> 613-642, 900 1533 -> 1191;
+// 257-384 rows (six rounds and a rest for three rows of small tiles) are even, 604
+// against 601, and stay with the small ones. k = 512, 600 rows: small 311, wide 402.
+// Up to 128 rows one row of small tiles reads the weights once (291 us against 413).
 int64_t logits_wide_columns(const Gemm& g) {
   constexpr int64_t LOGITS_REST = 64;
   const int64_t mt = ((int64_t)g.n_rows + PM - 1) / PM, nt = ((int64_t)g.n + PN - 1) / PN, tiles = mt * nt;
@@ -542,7 +545,7 @@ int64_t logits_wide_columns(const Gemm& g) {
   const bool split = rest > 0 && rest <= LOGITS_REST;
   const int64_t half_rounds = split ? tiles / 256 * 2 + 1 : (tiles + 255) / 256 * 2;
   const int64_t small = ((int64_t)g.n_rows + 127) / 128 * (((int64_t)g.n + 127) / 128);
-  if (g.n_rows < 1024 && 363 * half_rounds >= small) return 0;
+  if (g.n_rows < 1024 && half_rounds * (15.0 + 0.01145 * g.k) >= small * (0.0216 + 0.0000371 * g.k)) return 0;
   return split ? nt_full * PN : g.n;
 }
 

@@ -128,7 +128,7 @@ def test_lm_head_sample_wide_tiles(T, vocab, temperature):
     (130 and 400 rows), whole rounds only (256 rows), and a partial last tile in
     both directions (1030 rows, 33040 ids); targets on both sides of the cut and
     in the last slot."""
-    H = 256
+    H = 1280
     Wt, head = _small_head(H, vocab, 2011)
     rng = np.random.default_rng(T + vocab)
     x = torch.from_numpy(rng.standard_normal((T, H)).astype(np.float32) * 2)
@@ -150,7 +150,7 @@ def test_lm_head_sample_columns_of_160(T, vocab, cut, temperature):
     tiles leave over) that are a multiple of 160 and not of 128 and make enough
     tiles for the 64-row ones: every 64-column record is written once. Targets
     in columns 128-223 of runs of 320 columns."""
-    H = 256
+    H = 1280
     Wt, head = _small_head(H, vocab, 2021)
     rng = np.random.default_rng(T + vocab)
     x = torch.from_numpy(rng.standard_normal((T, H)).astype(np.float32) * 2)
@@ -167,7 +167,7 @@ def test_lm_head_sample_columns_of_160(T, vocab, cut, temperature):
 def test_lm_head_sample_off_16_byte_boundary():
     """Vocabulary rows that start 8 bytes past a 16-byte boundary, which direct
     loads to LDS are not used on, at a size of the wide tiles."""
-    H, vocab, T = 256, 131072, 256
+    H, vocab, T = 1280, 131072, 256
     Wt = W.lm_weights_host(2011, H, vocab, embed=False)
     buf = torch.empty(vocab * H + 4, dtype=torch.bfloat16, device="cuda")
     buf[4:].copy_(Wt["w_lm"].view(-1))
