@@ -1,7 +1,8 @@
 // Grouped GEMM whose operands reach LDS by direct loads through rings of 64-wide
 // reduction slices (gfx950, bf16 activations, bf16 or MXFP4 weights): the MXFP4
-// experts from 8 rows in all, bf16 experts of 48-255 rows each and the dense
-// projections between about a thousand and ten thousand rows.
+// experts from 8 rows in all, bf16 experts of 56 rows each and more and the dense
+// projections between about a thousand and ten thousand rows (those that the
+// pipelined kernel does not take).
 //
 // A workgroup owns a BM x BN output tile (token rows x weight rows): WM x WN
 // wavefronts multiply, and PX + PW producer wavefronts only request slices, by
@@ -62,6 +63,8 @@ constexpr int RK = 64;                   // reduction indices per slice
 constexpr int RBUF_D3 = 0x00020000;      // raw buffer descriptor word 3 (gfx9 family)
 constexpr int RING_MAX_KB = 96;          // MXFP4: scale blocks per weight row that the LDS plan holds
 constexpr int RING_DENSE_TILES = 300;    // bf16 matrices: 128 x 128 tiles from which the ring is taken
+constexpr int RING_MIN_ROWS = 56;        // bf16 experts: rows per group
+constexpr int RING_MIN_WORK = 65536;     // ... and tiles (rows even over the groups) times reduction
 constexpr int RXROW = RK * 2;            // bytes of a staged activation row
 
 __device__ __forceinline__ u32x4 lds16(const uint8_t* p) { return *reinterpret_cast<const u32x4*>(p); }
@@ -619,8 +622,14 @@ hipError_t ring_launch(const Gemm& g, hipStream_t s) {
 
 // Whether the ring takes a launch. MXFP4 experts from 8 rows in all (both
 // projections, slabs -> ring: one token 38 -> 41 us, two 58 -> 51). bf16 experts
-// from 48 rows each up to the pipelined kernel's 256 (64 rows: 383 -> 327 us, 125
-// rows 477 -> 433; 45 rows: slower, the 64-row tiles waste less) and one matrix
+// from RING_MIN_ROWS rows each, as far as the pipelined kernel does not take them
+// (32 experts, 2880 x 5760 and 2880 x 2880 together, 64-row tiles -> ring, rows even
+// / Zipf: 48 rows 306 -> 317 / 345 -> 384 us, 52 306 -> 323 / 370 -> 376, 56 334 ->
+// 326 / 396 -> 393, 64 390 -> 334 / 410 -> 382, 125 504 -> 457 / 523 -> 485), if the
+// launch has enough work to repay the ring's start (RING_MIN_WORK: 128-wide tiles
+// times reduction; 8 experts of 512 x 1024 at 100 rows 9 -> 10 us, of 1024 x 2048
+// 16 -> 14; where few tiles a CU meet uneven rows either side can win, 16 experts
+// of 2048 x 4096 at 56 rows 65 -> 56 / 65 -> 73). One matrix
 // from 300 tiles of 128 x 128 (QKV of 1408 rows 84 -> 71 us, of 3008 175 -> 119;
 // O of 1888 99 -> 77, of 5008 213 -> 146; fewer tiles leave CUs idle: QKV of 512
 // rows 38 -> 46).
@@ -640,7 +649,10 @@ bool ring_gemm_applies(int dtype, int expert_fmt, const Gemm& g) {
   if (g.epi == EPI_QKV && (g.n % 64 || (g.head_dim != 32 && g.head_dim != 64))) return false;
   if (pipe_gemm_applies(dtype, g)) return false;
   const int64_t groups = g.group_off ? g.n_groups : 1, tiles = ((int64_t)g.n_rows + 127) / 128 * ((g.n + 127) / 128);
-  if (g.group_off) return g.n_rows >= 48 * groups;
+  if (g.group_off) {
+    const int64_t even = groups * ((g.n_rows + 128 * groups - 1) / (128 * groups)) * ((g.n + 127) / 128);
+    return g.n_rows >= RING_MIN_ROWS * groups && even * g.k >= RING_MIN_WORK;
+  }
   return tiles >= RING_DENSE_TILES;
 }
 
