@@ -620,6 +620,28 @@ hipError_t ring_launch(const Gemm& g, hipStream_t s) {
 
 }  // namespace
 
+// m-tiles of `bm` rows if the rows fall evenly on the groups (by chance where there are few)
+static double even_m_tiles(const Gemm& g, int bm) {
+  const double G = g.n_groups, avg = g.n_rows / G;
+  return avg < 4 ? G * (1 - std::pow(1 - 1 / G, g.n_rows)) : G * std::ceil(avg / bm);
+}
+
+// MXFP4: whether the launch has enough work to repay the ring's start and its
+// wide tiles, by its 256-wide tiles and, where those are few, their reduction.
+// Against weight slabs (up to SLAB_MAX_ROWS_FP4 rows per group): gate/up of short
+// groups needs more than 128 tiles, as up to there slabs, half as wide, still find
+// a CU each (slab -> ring: 45 tiles of 64 experts 15 -> 19 us, 103 of 16 experts 16
+// -> 20, 165 of 32 experts 28 -> 25); from 12 rows, and for the down projection, only
+// tiny launches do not pay (8 experts of 576 x 640 8 -> 10 us, of 1024 x 2048 even).
+// Against the register-loading tiles above: 8 experts of 512 x 1024 at 128 rows
+// 13 -> 16 us, at 500 24 -> 17; of 1024 x 2048 at 128 23 -> 22.
+static bool mxfp4_ring_pays(const Gemm& g) {
+  const double avg = (double)g.n_rows / g.n_groups;
+  const double tiles = even_m_tiles(g, avg <= 40 ? 64 : 128) * ((g.n + 255) / 256), work = tiles * g.k;
+  if (avg > SLAB_MAX_ROWS_FP4) return work >= 65536;
+  return work >= 16384 && (g.epi == EPI_BIAS || avg >= 12 || tiles > 128);
+}
+
 // Whether the ring takes a launch. MXFP4 experts from 8 rows in all (both
 // projections, slabs -> ring: one token 38 -> 41 us, two 58 -> 51). bf16 experts
 // from RING_MIN_ROWS rows each, as far as the pipelined kernel does not take them
@@ -641,7 +663,7 @@ bool ring_gemm_applies(int dtype, int expert_fmt, const Gemm& g) {
   if (xr * g.k * 2 >= (1LL << 31) || (int64_t)g.n * g.k * 2 >= (1LL << 31)) return false;
   if (expert_fmt != 0)  // the tile's scales are staged whole, 16 bytes at a time
     return g.n_rows >= 8 && g.k <= 32 * RING_MAX_KB && g.w_scales && (uintptr_t)g.w_scales % 16 == 0 &&
-           (uintptr_t)g.w % 16 == 0 && (g.epi == EPI_SWIGLU || g.epi == EPI_BIAS);
+           (uintptr_t)g.w % 16 == 0 && (g.epi == EPI_SWIGLU || g.epi == EPI_BIAS) && mxfp4_ring_pays(g);
   if (g.w_packed && (int64_t)(g.n / 16) * ((g.k + 127) / 128) * 4096 >= (1LL << 31)) return false;
   // 16-byte direct loads to LDS are used on 16-byte aligned matrices only (token
   // rows come from the workspace); others keep the kernels that load to registers
@@ -658,13 +680,11 @@ bool ring_gemm_applies(int dtype, int expert_fmt, const Gemm& g) {
 
 hipError_t launch_gemm_ring(int expert_fmt, const Gemm& g, hipStream_t s) {
   if (expert_fmt != 0) {
-    // m-tiles of `bm` rows if the rows fall evenly on the groups
-    const double G = g.n_groups, avg = g.n_rows / G;
-    auto m_tiles = [&](int bm) { return avg < 4 ? G * (1 - std::pow(1 - 1 / G, g.n_rows)) : G * std::ceil(avg / bm); };
+    const double avg = (double)g.n_rows / g.n_groups;
     // 256-wide n-tiles, or 192-wide where the last round of 256 workgroups is
     // then better filled
     auto narrow = [&](int bm) {
-      auto cost = [&](int bn) { return std::ceil(m_tiles(bm) * ((g.n + bn - 1) / bn) / 256) * bn; };
+      auto cost = [&](int bn) { return std::ceil(even_m_tiles(g, bm) * ((g.n + bn - 1) / bn) / 256) * bn; };
       return g.epi == EPI_BIAS && 10 * cost(192) < 9 * cost(256);
     };
     if (avg <= 40)

@@ -31,29 +31,37 @@ def _forced_moe(s, weights, force, seed):
     return h, out.cpu().double().numpy(), mcpu.mcpu_check_device_errors(ws)
 
 
-# rows of experts 0..: around 32-row fragments, 64- and 128-row tiles, none, and
-# one expert holding nearly all (the 40- and 512-row averages of the dispatch)
+# rows of every eight experts: around 32-row fragments, 64- and 128-row tiles, none, and
+# experts holding nearly all (the 12-, 40- and 512-row averages of the dispatch)
 ROWS = {"few": [1, 2, 0, 3, 1, 0, 2, 1], "tile64": [31, 32, 33, 63, 64, 0, 65, 24],
         "tile128": [127, 128, 129, 96, 97, 0, 1, 255], "hot": [900, 0, 1, 0, 0, 5, 0, 0], "many": [700, 513, 512, 640, 515, 600, 530, 777]}
 
 
 @pytest.mark.parametrize("rows", list(ROWS))
-# 1, 3, 9 and 17 slices (half last units, the ring padded and full), n 32 .. 640 columns past whole tiles
-@pytest.mark.parametrize("hidden,ffn", [(64, 320), (192, 64), (576, 192), (1088, 128)])
+# gate/up reductions of 1, 3, 9 and 17 slices and down ones of 5 to 40 (half last units, the
+# ring padded and full), 64 .. 5120 columns past whole tiles; 64 experts, so that the work
+# is worth the ring
+@pytest.mark.parametrize("hidden,ffn", [(64, 2560), (192, 1088), (576, 448), (1088, 320)])
 def test_mxfp4_rows_and_reductions(hidden, ffn, rows):
-    s = _shape(hidden, ffn, top_k=1)
+    s = _shape(hidden, ffn, experts=64, top_k=1)
     wl = W.custom(s, [4], [1], 2101 + hidden)
-    force = np.random.default_rng(3).permutation(np.repeat(np.arange(8), ROWS[rows])).astype(np.int32)[:, None]
+    force = np.random.default_rng(3).permutation(np.repeat(np.arange(64), ROWS[rows] * 8)).astype(np.int32)[:, None]
     h, out, err = _forced_moe(s, wl.weights, force, 11)
     assert err == 0
-    PT.check("moe out", out, O.moe(s, O.Weights(s, wl.weights), h, force_idx=force)["out"], "bf16")
+    T = len(force)
+    pick = np.arange(T)
+    if T > 400:  # all rows of a few experts, and some of the others
+        pick = np.flatnonzero(np.isin(force[:, 0], [6, 34, 63]))
+        pick = np.unique(np.concatenate([pick, np.random.default_rng(4).choice(T, 200, replace=False)]))
+    ref = O.moe(s, O.Weights(s, wl.weights), h[torch.from_numpy(pick)], force_idx=force[pick])["out"]
+    PT.check("moe out", out[pick], ref, "bf16")
 
 
-@pytest.mark.parametrize("T", [40, 400])
+@pytest.mark.parametrize("T", [320, 3200])
 def test_mxfp4_rejected_scales_contribute_nothing(T):
     """Scales outside [2, 252], anywhere in a tile, raise the error bit, and the
     result is that of the same weights with those blocks' codes zero."""
-    s = _shape(576, 576)
+    s = _shape(576, 576, experts=64)
     wl = W.custom(s, [4], [1], 2111)
     rng = np.random.default_rng(5)
     bad, zero = dict(wl.weights), dict(wl.weights)
@@ -61,28 +69,28 @@ def test_mxfp4_rejected_scales_contribute_nothing(T):
         sc, codes = wl.weights[key + "_scales"].clone(), wl.weights[key + "_codes"].clone()
         E, R, B = sc.shape
         for v in (0, 1, 253, 254, 255):
-            for _ in range(6):
+            for _ in range(48):
                 e, r, b = int(rng.integers(E)), int(rng.integers(R)), int(rng.integers(B))
                 sc[e, r, b] = v
                 codes[e, r, 16 * b:16 * b + 16] = 0
         sc[0, 0, 0], sc[-1, -1, -1] = 255, 0
         codes[0, 0, :16], codes[-1, -1, -16:] = 0, 0
         bad[key + "_scales"], zero[key + "_codes"] = sc, codes
-    force = rng.integers(0, 8, size=(T, 2)).astype(np.int32)
+    force = rng.integers(0, 64, size=(T, 2)).astype(np.int32)
     _, want, err0 = _forced_moe(s, zero, force, 12)
     _, got, err = _forced_moe(s, bad, force, 12)
     assert err0 == 0 and err & mcpu.DEVERR_MXFP4
     np.testing.assert_array_equal(got, want)
 
 
-@pytest.mark.parametrize("T", [40, 400, 2400])  # 10, 100 and 600 rows per expert
+@pytest.mark.parametrize("T", [320, 3200, 19200])  # 10, 100 and 600 rows per expert
 @pytest.mark.parametrize("key", ["w_gu", "w_d"])
 def test_mxfp4_rejected_blocks_are_exactly_zero(key, T):
     """One matrix holds codes 6 in blocks of rejected scales and zeros elsewhere,
     so the experts add exactly nothing. Gate/up: a remainder of 2^-125 would
     come back through down weights of 6 x 2^125. Down: the rows are zero and the
     activations 56 (gate and up biases of 7), so a remainder is the output."""
-    s = _shape(576, 576)
+    s = _shape(576, 576, experts=64)
     wl = W.custom(s, [4], [1], 2112)
     rng = np.random.default_rng(6)
     w = {k: v.clone() for k, v in wl.weights.items()}
@@ -104,7 +112,7 @@ def test_mxfp4_rejected_blocks_are_exactly_zero(key, T):
     out = torch.full((T, s.hidden), 7.0, device="cuda")
     ws = mcpu.workspace(mcpu.moe_forward_workspace_size(s, T))
     mcpu.moe_forward(s, mcpu.DeviceWeights(s, w), h.cuda(), out, None, None,
-                     torch.from_numpy(rng.integers(0, 8, size=(T, 2)).astype(np.int32)).cuda(), ws)
+                     torch.from_numpy(rng.integers(0, 64, size=(T, 2)).astype(np.int32)).cuda(), ws)
     torch.cuda.synchronize()
     assert mcpu.mcpu_check_device_errors(ws) & mcpu.DEVERR_MXFP4
     assert torch.equal(out.cpu(), h)
