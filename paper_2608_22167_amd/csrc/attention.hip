@@ -552,7 +552,8 @@ hipError_t launch_attn_split(int dtype, int head_dim, const AttnSplit& p, hipStr
 // rows at a time: about 0.33 us per split of the longest list, but no cross-lane
 // steps and a fifth of the registers, where WIDE takes about 0.44 us per
 // thousand wavefronts. The shorter of the two is taken (wide -> in order: 512
-// tokens of one to 15 splits 18.4 -> 10.0 us, 9000 of one 204 -> 116).
+// tokens of one to 15 splits 18.4 -> 10.0 us, 9000 of one 204 -> 116); lists of
+// up to four are one round of loads either way and go in order.
 constexpr int COMBINE_WAVES = 65536;
 constexpr int COMBINE_WAVES_PER_SPLIT = 750;  // 0.33 us of a split in order, in wavefronts of the wide form
 
@@ -669,7 +670,7 @@ hipError_t launch_attn_combine(int dtype, int head_dim, const AttnCombine& p, hi
   const int64_t per_dec = std::max(1, p.n_tokens / std::max(p.n_dec, 1));
   const int K = (int)std::min<int64_t>({64, (waves + COMBINE_WAVES - 1) / COMBINE_WAVES, per_dec});
   const int stride = (p.n_tokens + K - 1) / K;
-  const bool wide = (int64_t)p.max_splits * COMBINE_WAVES_PER_SPLIT > (int64_t)p.n_dec * p.hq;
+  const bool wide = p.max_splits > 4 && (int64_t)p.max_splits * COMBINE_WAVES_PER_SPLIT > (int64_t)p.n_dec * p.hq;
   dim3 grid((unsigned)(((int64_t)stride * p.hq + 3) / 4)), block(256);
 #define COMBINE(T, D)                                                                                        \
   do {                                                                                                       \
