@@ -97,12 +97,13 @@ def test_lm_head_sample_small(T, vocab, temperature):
     print(f"  T={T} V={vocab} temperature={temperature}: {near} near-tie rows")
 
 
-@pytest.mark.parametrize("T", [64, 256, 512])
-def test_lm_head_sample_full_vocabulary_sampled(T):
-    """gpt-oss-20b shapes: hidden 2880, 201088 ids (1.16 GB of bf16 weights),
-    64 rows (streaming-order weight slabs), 256 rows (the benchmarked head) and
-    512 rows (128 x 128 tiles, records folded from the product registers);
-    compared on seeded rows."""
+@pytest.mark.parametrize("T,temperature", [(64, TAU), (128, TAU), (128, 0.0), (256, TAU), (300, TAU), (300, 0.0), (512, TAU)])
+def test_lm_head_sample_full_vocabulary_sampled(T, temperature):
+    """gpt-oss-20b shapes: hidden 2880, 201088 ids (1.16 GB of bf16 weights):
+    64 rows (streaming-order weight slabs), 128 and 300 rows (128 x 128 tiles,
+    records folded from the product registers, the second with a ragged last
+    tile), 256 rows (the benchmarked head) and 512 rows (256 x 256 tiles and
+    64 x 64 ones over the columns left over); compared on seeded rows."""
     H, V = 2880, W.GPT_OSS_VOCAB
     Wd = W.lm_weights_device(2002, H, V)
     head = mcpu.DeviceLmHead(Wd["g_final"], Wd["w_lm"])
@@ -111,10 +112,10 @@ def test_lm_head_sample_full_vocabulary_sampled(T):
     seq = rng.integers(0, 4096, T)
     pos = rng.integers(0, 65536, T)
     tgt = rng.integers(0, V, T)
-    gpu = _run_head(head, x, TAU, 5, seq, pos, tgt)
+    gpu = _run_head(head, x, temperature, 5, seq, pos, tgt)
     rows = np.unique(np.concatenate([[0, T - 1], rng.choice(T, 3, replace=False)]))
     w_host = W.synth_normal(2002, W.LM_TID["w_lm"], (V, H), std=0.02, dtype=torch.bfloat16)
-    ref = O.lm_head(x[torch.from_numpy(rows)], Wd["g_final"].cpu(), w_host, 1e-5, TAU, seed=5, seq_ids=seq[rows],
+    ref = O.lm_head(x[torch.from_numpy(rows)], Wd["g_final"].cpu(), w_host, 1e-5, temperature, seed=5, seq_ids=seq[rows],
                     positions=pos[rows], targets=tgt[rows], want_logits=True)
     near = _check(gpu, ref, rows)
     print(f"  T={T}: rows {rows.tolist()}, {near} near-tie rows, tokens {gpu['tokens'][rows].tolist()}")

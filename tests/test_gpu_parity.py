@@ -481,25 +481,27 @@ def test_projections_packed_weights_bitwise_equal_row_major(T):
 @pytest.mark.parametrize("fmt", ["dense", "mxfp4"])
 @pytest.mark.parametrize("hidden,ffn,T", [(512, 512, 1000), (1024, 1024, 3600)])
 def test_moe_forward_many_rows(fmt, hidden, ffn, T):
-    """Expert GEMMs with hundreds of rows per expert (64- and 128-row tiles,
-    ragged last tiles in every group)."""
+    """Expert GEMMs with 250 (64-row tiles; bf16 gate/up on the ring) and 900
+    rows per expert (the ring's 128-row tiles), ragged last tiles in every
+    group."""
     _moe_forward_check(_moe_shape(hidden, ffn, fmt), T, 1071 + hidden, 4)
 
 
 @pytest.mark.parametrize("fmt,T", [("dense", 40), ("mxfp4", 200), ("mxfp4", 350)])
 def test_moe_forward_slab_rows(fmt, T):
     """Expert GEMMs on weight slabs: about 10 (bf16 weights, from the
-    streaming-order copy; 64-row items) or 50 and 90 (MXFP4; 128-row items)
-    rows per expert, so every group is one item with a ragged end; 576 = 4.5
-    reduction chunks, so the last chunk is a half."""
+    streaming-order copy; 64-row items) or 50 and 90 (MXFP4 down projection;
+    128-row items; its gate/up runs on the ring) rows per expert, so every group
+    is one item with a ragged end; 576 = 4.5 reduction chunks, so the last chunk
+    is a half."""
     _moe_forward_check(_moe_shape(576, 576, fmt), T, 1075, 6)
 
 
 def test_moe_forward_mxfp4_slab_hot_expert():
-    """MXFP4 slabs with one expert far above the average: every one of 300
-    tokens picks expert 0 (300 rows: two full 128-row items and a ragged
-    third) and one of experts 1-7 (about 43 rows each, one item), 75 rows per
-    expert on average."""
+    """MXFP4 with one expert far above the average: every one of 300 tokens picks
+    expert 0 (300 rows: two full 128-row items and a ragged third) and one of
+    experts 1-7 (about 43 rows each, one item), 75 rows per expert on average;
+    gate/up in the ring's tiles, the down projection on slabs."""
     s = _moe_shape(576, 576, "mxfp4")
     T = 300
     wl = W.custom(s, [4], [1], 1095)
@@ -516,8 +518,9 @@ def test_moe_forward_mxfp4_slab_hot_expert():
 
 
 def test_dense_projections_ragged_rows_sampled():
-    """300 decode tokens: the dense projections take 64-row tiles with a ragged
-    last tile; compared on sampled sequences."""
+    """300 decode tokens: the dense projections with a ragged last tile (QKV on
+    weight slabs from the streaming-order copy, O in 64-row tiles); compared on
+    sampled sequences."""
     rng = np.random.default_rng(1081)
     ctx = rng.integers(1, 400, size=300)
     wl = W.custom(W.GPT_OSS_20B, ctx, np.ones(300), 1081)
@@ -599,8 +602,8 @@ def test_split_projections_repeatable_sampled():
 
 @pytest.mark.parametrize("fmt", ["dense", "mxfp4"])
 def test_moe_forward_large_groups_sampled(fmt):
-    """16384 tokens routed over the experts (thousands of rows each): the
-    128 x 128-tile path with many tiles per group; tokens are independent given their routing, so a seeded sample of
+    """16384 tokens routed over the experts (thousands of rows each): 256 x 256
+    tiles (bf16) and the ring (MXFP4) with many tiles per group; tokens are independent given their routing, so a seeded sample of
     rows is compared (the grouping still covers every token)."""
     s = _moe_shape(1024, 1024, fmt)
     T = 16384
@@ -628,8 +631,8 @@ def test_moe_forward_large_groups_sampled(fmt):
 
 
 def test_dense_projections_large_rows_sampled():
-    """8200 decode tokens: the dense projections take 128 x 128 tiles with a
-    ragged last tile; compared on sampled sequences."""
+    """8200 decode tokens: QKV takes 256 x 256 tiles and O the ring's 128 x 128
+    ones, each with a ragged last tile; compared on sampled sequences."""
     rng = np.random.default_rng(1093)
     ctx = rng.integers(1, 64, size=8200)
     wl = W.custom(W.GPT_OSS_20B, ctx, np.ones(8200), 1093)

@@ -31,6 +31,15 @@ def _forced_moe(s, weights, force, seed):
     return h, out.cpu().double().numpy(), mcpu.mcpu_check_device_errors(ws)
 
 
+def _shifted(t, n=4):
+    """A copy on the GPU that starts n elements past a 16-byte boundary."""
+    buf = torch.empty(t.numel() + n, dtype=t.dtype, device="cuda")
+    out = buf[n:].view(t.shape)
+    out.copy_(t)
+    assert out.data_ptr() % 16 and out.is_contiguous()
+    return out
+
+
 # rows of every eight experts: around 32-row fragments, 64- and 128-row tiles, none, and
 # experts holding nearly all (the 12-, 40- and 512-row averages of the dispatch)
 ROWS = {"few": [1, 2, 0, 3, 1, 0, 2, 1], "tile64": [31, 32, 33, 63, 64, 0, 65, 24],
@@ -53,6 +62,27 @@ def test_mxfp4_rows_and_reductions(hidden, ffn, rows):
     if T > 400:  # all rows of a few experts, and some of the others
         pick = np.flatnonzero(np.isin(force[:, 0], [6, 34, 63]))
         pick = np.unique(np.concatenate([pick, np.random.default_rng(4).choice(T, 200, replace=False)]))
+    ref = O.moe(s, O.Weights(s, wl.weights), h[torch.from_numpy(pick)], force_idx=force[pick])["out"]
+    PT.check("moe out", out[pick], ref, "bf16")
+
+
+# outside the ring: 98 scale blocks per weight row, more than its plan of LDS holds, or scales
+# that do not start on 16 bytes; rows per expert of weight slabs (one 64-row item, one and two
+# half ones of 128), of 64 x 128, 128 x 128 and 256 x 256 tiles (gate/up; down stays one smaller)
+@pytest.mark.parametrize("hidden,rows,shift", [(3136, 12, 0), (3136, 60, 0), (3136, 90, 0), (3136, 120, 0), (3136, 300, 0),
+                                               (3136, 700, 0), (1088, 20, 4), (1088, 110, 4)])
+def test_mxfp4_beyond_the_ring(hidden, rows, shift):
+    s = _shape(hidden, hidden, top_k=1)
+    wl = W.custom(s, [4], [1], 2113)
+    w = dict(wl.weights)
+    if shift:
+        for key in ("w_gu_scales", "w_d_scales"):
+            w[key] = _shifted(w[key], shift)
+    rng = np.random.default_rng(7)
+    force = rng.permutation(np.repeat(np.arange(8), rows)).astype(np.int32)[:, None]
+    h, out, err = _forced_moe(s, w, force, 16)
+    assert err == 0
+    pick = np.unique(np.concatenate([[0, len(force) - 1], rng.choice(len(force), 60, replace=False)]))
     ref = O.moe(s, O.Weights(s, wl.weights), h[torch.from_numpy(pick)], force_idx=force[pick])["out"]
     PT.check("moe out", out[pick], ref, "bf16")
 
@@ -139,15 +169,6 @@ def test_bf16_experts(pack, ffn):
                                      np.random.default_rng(4).choice(T, 300, replace=False)]))
     ref = O.moe(s, O.Weights(s, wl.weights), h[torch.from_numpy(pick)], force_idx=force[pick])["out"]
     PT.check("moe out", out.cpu().double().numpy()[pick], ref, "bf16")
-
-
-def _shifted(t, n=4):
-    """A copy on the GPU that starts n elements (8 bytes in bf16) past a 16-byte boundary."""
-    buf = torch.empty(t.numel() + n, dtype=t.dtype, device="cuda")
-    out = buf[n:].view(t.shape)
-    out.copy_(t)
-    assert out.data_ptr() % 16 and out.is_contiguous()
-    return out
 
 
 @pytest.mark.parametrize("T", [700, 16384])  # about 88 and 2048 rows per expert: ring and 256 x 256 tiles if aligned
