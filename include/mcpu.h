@@ -126,8 +126,9 @@ typedef struct mcpu_layer_cfg {
  *    aligned; the products read only these.
  *  w_qkv_packed, w_o_packed  optional (NULL): bf16 w_qkv and w_o in the same
  *    streaming order (mcpu_pack_weights with one group, rows in their own
- *    order), read by the projections of steps of up to 64 tokens and by the
- *    O projection of prefill-sized steps; w_qkv and w_o stay required. */
+ *    order), read by the projections of steps of up to 64 tokens, by QKV of up
+ *    to 512, by both from about a thousand tokens on and by the O projection of
+ *    prefill-sized steps; w_qkv and w_o stay required. */
 typedef struct mcpu_layer_weights {
   const float* g1;
   const void* w_qkv;

@@ -1,8 +1,8 @@
 // Grouped GEMM whose operands reach LDS by direct loads through rings of 64-wide
 // reduction slices (gfx950, bf16 activations, bf16 or MXFP4 weights): the MXFP4
-// experts from 8 rows in all, bf16 experts of 56 rows each and more and the dense
-// projections between about a thousand and ten thousand rows (those that the
-// pipelined kernel does not take).
+// experts from 8 rows in all and bf16 experts from 56 rows each, where the launch
+// repays its start, and the dense projections between about a thousand and ten
+// thousand rows (bf16 as far as the pipelined kernel does not take them).
 //
 // A workgroup owns a BM x BN output tile (token rows x weight rows): WM x WN
 // wavefronts multiply, and PX + PW producer wavefronts only request slices, by
@@ -78,9 +78,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t ring_rsrc(const void* base) {
 }
 
 // 16 bytes per lane to LDS, lane l at byte 16 l
-template <int AUX = 0>
 __device__ __forceinline__ void to_lds16(__amdgpu_buffer_rsrc_t r, uint8_t* dst, uint32_t vo, int so) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(dst), 16, vo, so, 0, AUX);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(dst), 16, vo, so, 0, 0);
 }
 
 // Weight row, within a wavefront's piece of 16 NT rows, that fragment nb holds
@@ -126,7 +125,7 @@ __device__ __forceinline__ RingGroups ring_groups(const Gemm& P, int lane) {
 
 // PX, PW: producer wavefronts for activations and weights; XS, CS: LDS stages
 // of each (powers of two, XS <= CS)
-template <int BM, int BN, int WM, int WN, int XS, int CS, int PX, int PW, int EPI, int WF, bool WP, int NTW>
+template <int BM, int BN, int WM, int WN, int XS, int CS, int PX, int PW, int EPI, int WF, bool WP>
 __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gemm P) {
   constexpr int NW = WM * WN;
   constexpr int MT = BM / 16 / WM, NT = BN / 16 / WN;  // 16-row fragments per wavefront
@@ -286,7 +285,7 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
         uint8_t* dst = lds + WOFF + (slot % CS) * WB + 1024 * p0;
         const int so = uniform(ks * (WP ? 2048 : WROW));
 #pragma unroll
-        for (int j = 0; j < WJ; ++j) to_lds16<NTW>(wr, dst + 1024 * j, vo[j], so);
+        for (int j = 0; j < WJ; ++j) to_lds16(wr, dst + 1024 * j, vo[j], so);
       };
       // MXFP4: an item's E8M0 scales, [row][k / 32], are staged whole, once the
       // item before is multiplied: their rows are consecutive in memory, so that
@@ -599,20 +598,24 @@ __global__ __launch_bounds__((WM * WN + PX + PW) * 64) void gemm_ring_kernel(Gem
   }
 }
 
-template <int BM, int BN, int WM, int WN, int XS, int CS, int PX, int PW, int WF, bool WP, int NTW = 0>
+template <int BM, int BN, int WM, int WN, int XS, int CS, int PX, int PW, int WF, bool WP>
 hipError_t ring_launch(const Gemm& g, hipStream_t s) {
   // one persistent workgroup per CU, eight XCDs
   dim3 gd((unsigned)std::min<int64_t>(tile_grid(g, BM, BN), 256)), bd((WM * WN + PX + PW) * 64);
-#define RING(E) hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WM, WN, XS, CS, PX, PW, E, WF, WP, NTW>), gd, bd, 0, s, g)
+#define RING(E) hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WM, WN, XS, CS, PX, PW, E, WF, WP>), gd, bd, 0, s, g)
   constexpr int NT = BN / 16 / WN;
   if constexpr (NT == 4 && WF == 0) {  // one matrix: the projections
     if (g.epi == EPI_QKV) RING(EPI_QKV);
     else if (g.epi == EPI_RESIDUAL) RING(EPI_RESIDUAL);
     else return hipErrorNotSupported;
   } else {
-    if (g.epi == EPI_BIAS) RING(EPI_BIAS);
-    else if (NT != 3 && g.epi == EPI_SWIGLU) RING(NT == 3 ? EPI_BIAS : EPI_SWIGLU);
-    else return hipErrorNotSupported;
+    if (g.epi == EPI_BIAS) {
+      RING(EPI_BIAS);
+    } else {
+      if constexpr (NT == 3) return hipErrorNotSupported;  // 192-wide tiles are the down projection's
+      else if (g.epi == EPI_SWIGLU) RING(EPI_SWIGLU);
+      else return hipErrorNotSupported;
+    }
   }
 #undef RING
   return hipGetLastError();

@@ -332,10 +332,12 @@ bool tiled_gemm_applies(int dtype, const Gemm& g) {
 // Tile choice by rows per group and the number of tiles a launch has: the
 // pipelined 256 x 256 kernel (gemm_pipe.hip) once groups average 256 rows
 // with two tiles per compute unit; else 128 x 128 tiles once they average 128
-// rows with a few tiles per compute unit; 64-row tiles otherwise (less
-// padding per group), 64 x 64 for a single dense matrix that would not fill
-// the chip. The 64-row tiles of decode batches stage two slices ahead (four
-// measured slower at batch 256).
+// rows with a few tiles per compute unit (the vocabulary head; other launches
+// of that size come here only where the ring kernel refuses them: matrices off
+// 16-byte boundaries or beyond 32-bit offsets, MXFP4 reductions over 3072);
+// 64-row tiles otherwise (less padding per group), 64 x 64 for a single dense
+// matrix that would not fill the chip. The 64-row tiles of decode batches stage
+// two slices ahead (four measured slower at batch 256).
 hipError_t launch_gemm_tiled(int expert_fmt, const Gemm& g, hipStream_t s) {
   if (expert_fmt != 0 && !g.w_scales) return hipErrorInvalidValue;
   if (pipe_gemm_applies(1, g)) {
