@@ -1007,7 +1007,8 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(AttnPrefill P) {
 // first visible keys score low.
 //
 // Bound: the vector pipe, about 126 instructions per wavefront and step (the 64
-// x 32 exponentials cost two slots each). Measured against the 16 x 16 tiles,
+// x 32 exponentials cost two slots each; counted 6.9 per product, the matrix cores
+// 47% busy). Measured against the 16 x 16 tiles,
 // 64 query heads on 8 KV heads: twelve chunks (32 K tokens) behind up
 // to 24 K keys 10.36 -> 8.27 ms, six chunks (1.8 K tokens) behind up to 16 K
 // 383 -> 273 us.
